@@ -619,6 +619,8 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
     __shared__ unsigned s_off[kMaxSites + 1];   // bucket offset of each head
     __shared__ unsigned s_tile[kMaxSites + 1];  // first tile of each head
     __shared__ unsigned s_q[2];                 // tile indices handed out by the queues
+    // queued tiles of each stretch: the first one and how many
+    __shared__ unsigned s_qfirst[kMlpQueues], s_qcount[kMlpQueues];
 
     const int tid = threadIdx.x, lane = tid & 63;
     // wave-uniform by construction; saying so keeps LDS-destination pointers scalar
@@ -669,28 +671,84 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
 
     // Tiles are handed out dynamically.  The tile range is cut into 8
     // contiguous stretches, one per XCD (each XCD has its own L2, and a
-    // stretch covers few heads); queue[x] counts the tiles taken from
-    // stretch x.  A workgroup takes from its own XCD's stretch, then from the
-    // others.  The two workgroups sharing a CU do not get equal shares of its
-    // matrix pipe, so static ranges would leave one finishing long after the
-    // other.  The counters are zero at launch (the bucket scan clears them).
+    // stretch covers few heads).  Workgroup b's first tile is fixed: the
+    // (b / 8)-th of stretch b % 8 (workgroups go to the XCDs in turn), so a
+    // launch of at most one tile per workgroup takes none from the queues.
+    // queue[x] counts the tiles taken from stretch x after those; a workgroup
+    // takes from its own XCD's stretch, then from the others.  The two
+    // workgroups sharing a CU do not get equal shares of its matrix pipe, so
+    // static ranges would leave one finishing long after the other.  The
+    // counters are zero at launch (the bucket scan clears them).
+    //
+    // An atomic on these counters (one cache line, all XCDs) is served in
+    // about 10 ns and the takes of a launch are served one after another, so
+    // a stretch that has run out is found from the counters' values (8 loads
+    // in flight at once), and a workgroup with nothing left asks no more.
+    // With an atomic on every stretch for each failing take, 512 workgroups
+    // spent about 90 us per launch on them, whatever its size: 32,768 samples
+    // of 4x64 fp32 heads 117 -> 26 us, a level of 0.3 M samples of 8x128 heads
+    // in the culled render 115 -> 38 us.  The stretches' first queued tile and
+    // count are kept in LDS: the kernel has no scalar registers to spare (in
+    // registers they cost the 6x64 heads 1 %).
     const unsigned xcc = (unsigned)__builtin_amdgcn_s_getreg(20 | (31 << 11)) & 7u;  // XCC_ID
-    auto q_base = [&](unsigned x) { return (unsigned)(((unsigned long long)total_tiles * x) / 8); };
-    // finish a take whose first attempt on the own stretch returned t
-    auto take_rest = [&](unsigned t) -> unsigned {
-        if (t < q_base(xcc + 1) - q_base(xcc))
-            return q_base(xcc) + t;
-        for (unsigned k = 1; k < 8; ++k) {
-            const unsigned x = (xcc + k) & 7u;
-            const unsigned u = atomicAdd(queue + x, 1u);
-            if (u < q_base(x + 1) - q_base(x))
-                return q_base(x) + u;
+    // take a tile of any stretch, from the own one on, or kNoTile: a failed
+    // atomic means that the stretch's counter has passed its end, so the next
+    // look skips it
+    auto steal = [&]() -> unsigned {
+        unsigned queued = 0;
+#pragma unroll
+        for (unsigned x = 0; x < (unsigned)kMlpQueues; ++x)
+            queued |= s_qcount[x];
+        if (queued == 0)
+            return kNoTile;  // no tiles but the fixed ones
+        for (;;) {
+            unsigned cnt[kMlpQueues];
+#pragma unroll
+            for (unsigned x = 0; x < (unsigned)kMlpQueues; ++x)
+                cnt[x] = __hip_atomic_load(queue + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            unsigned pick = kNoTile;
+#pragma unroll
+            for (unsigned x = 0; x < (unsigned)kMlpQueues; ++x)
+                if (cnt[x] < s_qcount[x] && (pick == kNoTile || ((x - xcc) & 7u) < ((pick - xcc) & 7u)))
+                    pick = x;
+            if (pick == kNoTile)
+                return kNoTile;
+            const unsigned u = atomicAdd(queue + pick, 1u);
+            if (u < s_qcount[pick])
+                return s_qfirst[pick] + u;
         }
-        return kNoTile;
     };
+    // the own stretch's queued tiles, 0 once it has run out, and their first
+    // (thread 0's, in registers: a take that waited for an LDS read held up
+    // its workgroup at every tile)
+    unsigned own = 0, own_first = 0;
+    // finish a take: the own stretch's atomic returned u (not asked when own == 0)
+    auto take_rest = [&](unsigned u) -> unsigned {
+        if (u < own)
+            return own_first + u;
+        own = 0;
+        return steal();
+    };
+    auto q_base = [&](unsigned x) { return (unsigned)(((unsigned long long)total_tiles * x) / 8); };
+    if (tid < kMlpQueues) {
+        const unsigned x = (unsigned)tid, base = q_base(x), len = q_base(x + 1) - base;
+        const unsigned fixed = (gridDim.x + 7u - x) >> 3;  // first tiles that are fixed
+        s_qfirst[x] = base + fixed;
+        s_qcount[x] = len > fixed ? len - fixed : 0u;
+        if (x == (blockIdx.x & 7u))
+            s_q[0] = (blockIdx.x >> 3) < len ? base + (blockIdx.x >> 3) : kNoTile;
+    }
+    __syncthreads();
     if (tid == 0) {
-        s_q[0] = take_rest(atomicAdd(queue + xcc, 1u));
-        s_q[1] = take_rest(atomicAdd(queue + xcc, 1u));
+        own = s_qcount[xcc];
+        own_first = s_qfirst[xcc];
+        unsigned first = s_q[0];
+        if (first == kNoTile)
+            s_q[0] = first = steal();
+        unsigned u = 0;
+        if (first != kNoTile && own)
+            u = atomicAdd(queue + xcc, 1u);
+        s_q[1] = first != kNoTile ? take_rest(u) : kNoTile;
     }
     __syncthreads();
     unsigned tile = __builtin_amdgcn_readfirstlane(s_q[0]);
@@ -808,9 +866,13 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
         // take the tile after next: the attempt on the own stretch is issued
         // here and completes under the prologue's full wait below, so it
         // never disturbs the counted waits of the weight stream
-        unsigned q_first = 0;
-        if (tid == 0)
-            q_first = atomicAdd(queue + xcc, 1u);
+        // (the address goes through a vector register: for a uniform one the
+        // compiler combines the lanes' atomics and waits for the result, and
+        // for every load in flight, right here)
+        unsigned q_first = 0, q_own = xcc;
+        asm("" : "+v"(q_own));
+        if (tid == 0 && has_next && own)
+            q_first = atomicAdd(queue + q_own, 1u);
         if (head != loaded_head) {
             const unsigned char *src = reinterpret_cast<const unsigned char *>(blocks + (size_t)head * C::BLOCK_FLOATS);
             for (int u = wave; u < C::BLOCK_UNITS; u += C::WAVES)
@@ -870,7 +932,7 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
         }
         wait_all();  // weight stages 0..2 and the head block have landed
         if (tid == 0)
-            s_q[0] = take_rest(q_first);
+            s_q[0] = has_next ? take_rest(q_first) : kNoTile;
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // the store above
         wg_barrier();
 
@@ -1193,7 +1255,13 @@ hipError_t launch_mlp(const unsigned *bucket, const unsigned *totals, const unsi
     }();
     (void)raised;
     const Chunk<C> *gx = reinterpret_cast<const Chunk<C> *>(gxtab);
-    const dim3 grid(cus * C::WG_PER_CU), block(C::THREADS);
+    // as many persistent workgroups as fit, but no more than there can be
+    // tiles (each head's last one may be partial)
+    const unsigned long long heads_rows = soft ? num_sites : 1;
+    const unsigned long long tiles =
+        heads_rows * ((g.num_samples + (unsigned long long)C::TILE - 1) / C::TILE) + num_sites;
+    const unsigned long long fit = (unsigned long long)cus * C::WG_PER_CU;
+    const dim3 grid((unsigned)(tiles < fit ? tiles : fit)), block(C::THREADS);
     if constexpr (!C::GX) {
         if (soft) {
             mlp_kernel<C, true, false><<<grid, block, C::LDS_BYTES, s>>>(
