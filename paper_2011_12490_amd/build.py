@@ -17,9 +17,11 @@ LIB = os.path.join(PKG, "libderf.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-# the grouped MLP is instantiated per head architecture, one unit each, so
-# that its variants compile in parallel
-SOURCES = ["mlp_8x256.hip", "mlp_8x128.hip", "mlp_6x64.hip", "mlp_4x64.hip", "kernels_sample.hip",
+# the grouped MLP is instantiated per head architecture and arithmetic, one
+# unit each, so that its variants compile in parallel
+SOURCES = ["mlp_8x256.hip", "mlp_8x128.hip", "mlp_8x128_split.hip", "mlp_8x128_f32.hip",
+           "mlp_6x64.hip", "mlp_6x64_split.hip", "mlp_6x64_f32.hip", "mlp_4x64.hip",
+           "mlp_4x64_split.hip", "mlp_4x64_f32.hip", "kernels_sample.hip",
            "kernels_fine.hip", "kernels_soft.hip", "kernels_gate.hip", "derf_api.cpp"]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=" + ARCH,

@@ -932,6 +932,14 @@ int create_body(derf_handle **out, int num_sites, const float *sites_xyz,
         if (!isfinite(weights[i]))
             return fail(DERF_ERR_INVALID_ARG, "non-finite weight");
 
+    // a form that takes only some weights needs every head of its
+    // architecture to fit (one launch per architecture)
+    for (int k = 0; k < num_sites; ++k) {
+        const MlpVariant *v = head_v[k];
+        if (v->plain && !v->fits(weights + woff[k]))
+            std::replace(head_v.begin(), head_v.end(), v, v->plain);
+    }
+
     derf_handle *h = injected_failure() ? nullptr : new (std::nothrow) derf_handle();
     if (!h)
         return fail(DERF_ERR_OOM, "handle");

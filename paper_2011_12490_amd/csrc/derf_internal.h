@@ -159,6 +159,10 @@ struct MlpVariant {
     int pos_freqs;
     hipError_t (*encode)(const RenderGeometry &g, const float *t, void *gxtab, int cus,
                          hipStream_t s);
+    // a form for some weights only: whether a head's fit, and the form for
+    // the others (null: every head's fit)
+    const MlpVariant *plain;
+    bool (*fits)(const float *w);
 };
 
 // Returns nullptr when no kernel is compiled for this architecture/precision.
@@ -169,5 +173,13 @@ const MlpVariant *mlp_variant_4x64(bool bf16);
 const MlpVariant *mlp_variant_6x64(bool bf16);
 const MlpVariant *mlp_variant_8x128(bool bf16);
 const MlpVariant *mlp_variant_8x256(bool bf16);
+// float32 heads: the form on the fp16 matrix units (split operands), and the
+// form on the fp32 units that it names for weights that do not fit
+const MlpVariant *mlp_split_4x64();
+const MlpVariant *mlp_split_6x64();
+const MlpVariant *mlp_split_8x128();
+const MlpVariant *mlp_f32_4x64();
+const MlpVariant *mlp_f32_6x64();
+const MlpVariant *mlp_f32_8x128();
 
 }  // namespace derf

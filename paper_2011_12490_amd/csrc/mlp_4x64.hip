@@ -5,7 +5,7 @@ namespace derf {
 
 const MlpVariant *mlp_variant_4x64(bool bf16)
 {
-    return bf16 ? variant<Cfg<true, 64, 4, -1, 0, 6>>() : variant<Cfg<false, 64, 4, -1, 0, 6>>();
+    return bf16 ? variant<Cfg<P_BF16, 64, 4, -1, 0, 6>>() : mlp_split_4x64();
 }
 
 }  // namespace derf

@@ -1,0 +1,12 @@
+// Grouped per-head MLP variants: 4 layers of 64, no skip, colour straight from [h; gamma(d)] (pos_freqs 6).
+// float32 heads on the fp32 matrix units.
+#include "mlp_kernel.h"
+
+namespace derf {
+
+const MlpVariant *mlp_f32_4x64()
+{
+    return variant<Cfg<P_F32, 64, 4, -1, 0, 6>>();
+}
+
+}  // namespace derf

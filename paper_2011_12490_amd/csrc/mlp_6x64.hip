@@ -5,7 +5,7 @@ namespace derf {
 
 const MlpVariant *mlp_variant_6x64(bool bf16)
 {
-    return bf16 ? variant<Cfg<true, 64, 6, -1, 32, 10>>() : variant<Cfg<false, 64, 6, -1, 32, 10>>();
+    return bf16 ? variant<Cfg<P_BF16, 64, 6, -1, 32, 10>>() : mlp_split_6x64();
 }
 
 }  // namespace derf

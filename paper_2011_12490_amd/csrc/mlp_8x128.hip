@@ -5,7 +5,7 @@ namespace derf {
 
 const MlpVariant *mlp_variant_8x128(bool bf16)
 {
-    return bf16 ? variant<Cfg<true, 128, 8, 5, 64, 10>>() : variant<Cfg<false, 128, 8, 5, 64, 10>>();
+    return bf16 ? variant<Cfg<P_BF16, 128, 8, 5, 64, 10>>() : mlp_split_8x128();
 }
 
 }  // namespace derf

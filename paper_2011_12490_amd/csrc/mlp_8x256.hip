@@ -5,7 +5,7 @@ namespace derf {
 
 const MlpVariant *mlp_variant_8x256(bool bf16)
 {
-    return bf16 ? variant<Cfg<true, 256, 8, 5, 128, 10>>() : nullptr;
+    return bf16 ? variant<Cfg<P_BF16, 256, 8, 5, 128, 10>>() : nullptr;
 }
 
 }  // namespace derf

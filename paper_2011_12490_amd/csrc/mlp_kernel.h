@@ -40,6 +40,10 @@
 // density, rows 1-3 colour logits), so the network tail needs no cross-lane
 // reduction.
 #pragma once
+#include <math.h>
+#include <string.h>
+
+#include <algorithm>
 #include <type_traits>
 #include <vector>
 
@@ -53,6 +57,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef short i16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
 template <int N>
 using ic = std::integral_constant<int, N>;
@@ -77,20 +83,25 @@ __host__ __device__ constexpr int c_row(int g, int i) { return 8 * (i / 4) + 4 *
 // stages of at most UMAX units.
 enum { K_HID = 0, K_RGBH = 1, K_OUT = 2 };
 
-// A-fragment reads kept in flight ahead of the MFMA that uses them: during
-// step F (the F-th fragment of a tile) the wave reads fragment F + kPrefetch.
-constexpr int kPrefetch = 3;
+// Arithmetic of a configuration: fp32 products on the fp32 matrix units, bf16
+// operands, or fp32 operands split into two fp16 values (see Split below).
+enum { P_F32 = 0, P_BF16 = 1, P_SPLIT = 2 };
 
 // GX_: the stored-encoding form, which reads each sample's gamma(x) entries
 // from a table in HBM (gx_encode_kernel) instead of encoding them in the
 // tile prologue; kept to measure what the fusion saves.
-template <bool BF16_, int W_, int D_, int SKIP_, int RH_, int LP_, bool GX_ = false>
+template <int PREC_, int W_, int D_, int SKIP_, int RH_, int LP_, bool GX_ = false>
 struct Cfg {
-    static constexpr bool BF16 = BF16_;
+    static constexpr int PREC = PREC_;
+    static constexpr bool BF16 = PREC == P_BF16, SPLIT = PREC == P_SPLIT;
     static constexpr int W = W_, D = D_, SKIP = SKIP_, RH = RH_, LP = LP_;
     static constexpr bool GX = GX_;
-    static constexpr int E = BF16 ? 8 : 1;     // k-entries per lane per MFMA
-    static constexpr int CPU = BF16 ? 1 : 4;   // MFMA k-chunks per 1 KB unit
+    static constexpr int E = PREC == P_F32 ? 1 : 8;    // k-entries per lane per MFMA
+    static constexpr int CPU = PREC == P_F32 ? 4 : 1;  // MFMA k-chunks per 1 KB unit
+    static constexpr int UPC = SPLIT ? 2 : 1;  // units per k-chunk (split: low half, high half)
+    // A-fragment reads kept in flight ahead of the MFMA that uses them: during
+    // step F (the F-th fragment of a tile) the wave reads fragment F + PF.
+    static constexpr int PF = SPLIT ? 4 : 3;
     static constexpr int NB = BF16 ? 2 : 1;    // 32-sample column blocks per wave
     static constexpr int WAVES = 4;
     static constexpr int THREADS = WAVES * 64;
@@ -109,7 +120,7 @@ struct Cfg {
     static constexpr int ERH = MTR * 16;       // colour-hidden entries per lane
     static constexpr int EXC = EX / E, EHC = EH / E, EDC = ED / E, ERHC = ERH / E;
     static constexpr int UMAX = BF16 && W == 64 ? 4 : 8;  // units per stage
-    static constexpr int CMAX = UMAX * CPU;    // chunks per stage
+    static constexpr int CMAX = UMAX * CPU / UPC;  // chunks per stage
     static constexpr int NBUF = 8;             // LDS ring slots (power of two)
     static constexpr int G = 2;                // stages per barrier
     static constexpr int LA = 6;               // weight loads issued this many stages ahead
@@ -155,7 +166,7 @@ struct Cfg {
                 t.split[s] = k;
                 t.c0[s] = k * CMAX;
                 t.c1[s] = (k + 1) * CMAX < t_chunks(T) ? (k + 1) * CMAX : t_chunks(T);
-                t.units[s] = (t.c1[s] - t.c0[s]) / CPU;
+                t.units[s] = (t.c1[s] - t.c0[s]) * UPC / CPU;
                 t.lpw[s] = (t.units[s] + WAVES - 1) / WAVES;
             }
         t.off[0] = 0;
@@ -181,7 +192,7 @@ struct Cfg {
 
     // A fragments of a tile's stages, numbered consecutively: stage s's
     // fragment j is number foff(s) + j.  The register window holds fragment
-    // F in slot F % kPrefetch.
+    // F in slot F % PF.
     static constexpr int foff(int s) { return TAB.foff[s]; }
     static constexpr int FTOTAL = TAB.foff[NS];
     static constexpr int f_stage(int F)
@@ -219,7 +230,7 @@ struct Cfg {
     // group start a the wave issues the weight loads of stages a + LA ..
     // (the next tile's stages past the end), then the gamma(d) loads if a ==
     // S_GD.  Before the barrier of group a, the units of stage need(a) -- the
-    // last stage the group's fragment reads reach: kPrefetch fragments past
+    // last stage the group's fragment reads reach: PF fragments past
     // its last step, which is beyond the next stage when that one is shorter
     // (the 2-unit stages of the 8x256 colour layer) -- must have landed;
     // vm_allowed(a) counts this wave's memory operations issued
@@ -232,7 +243,7 @@ struct Cfg {
     static constexpr int need(int a)
     {
         const int next = grp_end(a) + 1 < NS ? grp_end(a) + 1 : grp_end(a);
-        const int fe = TAB.foff[grp_end(a) + 1] - 1 + kPrefetch;  // furthest fragment read
+        const int fe = TAB.foff[grp_end(a) + 1] - 1 + PF;  // furthest fragment read
         const int reach = f_stage(fe < FTOTAL ? fe : FTOTAL - 1);
         return reach > next ? reach : next;
     }
@@ -240,7 +251,7 @@ struct Cfg {
     static constexpr bool waits_cover_reads()
     {
         for (int a = 0; a < NS; a += G) {
-            const int fe = TAB.foff[grp_end(a) + 1] - 1 + kPrefetch;
+            const int fe = TAB.foff[grp_end(a) + 1] - 1 + PF;
             if ((fe < FTOTAL ? fe : FTOTAL - 1) >= TAB.foff[need(a) + 1])
                 return false;
         }
@@ -297,8 +308,14 @@ struct Cfg {
     // were issued at a later group start
     static_assert((need(S_PB) - LA) / G * G > S_PA, "prefetch phases too close");
 
-    // per-head resident block: bias of every output tile in accumulator layout
-    static constexpr int BLOCK_FLOATS = (NT * 32 + 255) / 256 * 256;
+    // per-head resident block: bias of every output tile in accumulator layout;
+    // split: then per hidden layer (the colour hidden layer last) the largest
+    // row sum of |W| and the largest |b|, then the output rows' factors
+    static constexpr int SC_OFF = NT * 32, SC_OUT = SC_OFF + 2 * (D + 1);
+    static constexpr int BLOCK_FLOATS = ((SPLIT ? SC_OUT + 4 : NT * 32) + 255) / 256 * 256;
+    // the split form's re-encode at the skip layer takes the scale fixed
+    // during the layer's second tile
+    static_assert(!SPLIT || SKIP < 0 || MT >= 4, "skip re-encode before its scale is known");
     static constexpr int BLOCK_UNITS = BLOCK_FLOATS / 256;
 
     // LDS: ring | head block | per wave: the next tile's sample records
@@ -346,6 +363,9 @@ constexpr int d_col(int g, int e) { return e < 8 ? 8 * g + e : 16 + 8 * g + (e -
 // ---------------------------------------------------------------------------
 // Host-side packing of one head (fp32 packed order of derf.h -> kernel layout).
 template <class C>
+struct Split;
+
+template <class C>
 struct Packer {
     struct View {
         const float *W;
@@ -372,54 +392,57 @@ struct Packer {
         }
     }
 
-    // weight of output tile T, row m (0..31 within the tile), lane group g, entry e
-    static float wval(const std::vector<View> &v, int T, int m, int g, int e)
+    // Row m (0..31) of output tile T: its weights, or null for a row of zeros.
+    // The output tile's row 0 is the density, rows 1..3 the colour logits.
+    static const float *tile_row(const std::vector<View> &v, int T, int m)
     {
         const int kind = C::t_kind(T);
+        const View &L = kind == K_HID    ? v[C::t_layer(T)]
+                        : kind == K_RGBH ? v[C::D + 1]
+                        : m == 0         ? v[C::D]
+                                         : v.back();
+        const int row = kind == K_OUT ? (m == 0 ? 0 : m - 1) : 32 * C::t_mt(T) + m;
+        return row < L.out ? L.W + (size_t)row * L.in : nullptr;
+    }
+    // The column of that row which entry e of lane group g multiplies, or -1.
+    static int tile_col(int T, int m, int g, int e)
+    {
+        const int kind = C::t_kind(T);
+        auto dir = [&](int q) { return d_col(g, q) < C::DD ? C::W + d_col(g, q) : -1; };
         if (kind == K_HID) {
-            const int l = C::t_layer(T);
-            const View &L = v[l];
-            const int row = 32 * C::t_mt(T) + m;
-            int col;
-            if (l == 0)
-                col = x_col<C>(g, e);
-            else if (l == C::SKIP)
-                col = e < C::EX ? x_col<C>(g, e) : C::P + h_col(g, e - C::EX);
-            else
-                col = h_col(g, e);
-            return col >= 0 ? L.W[(size_t)row * L.in + col] : 0.0f;
+            if (C::t_layer(T) == 0)
+                return x_col<C>(g, e);
+            if (C::t_layer(T) == C::SKIP)
+                return e < C::EX ? x_col<C>(g, e) : C::P + h_col(g, e - C::EX);
+            return h_col(g, e);
         }
-        if (kind == K_RGBH) {
-            const View &L = v[C::D + 1];
-            const int row = 32 * C::t_mt(T) + m;
-            if (row >= C::RH)
-                return 0.0f;
-            int col;
-            if (e < C::EH)
-                col = h_col(g, e);
-            else
-                col = d_col(g, e - C::EH) < C::DD ? C::W + d_col(g, e - C::EH) : -1;
-            return col >= 0 ? L.W[(size_t)row * L.in + col] : 0.0f;
+        if (kind == K_RGBH)
+            return e < C::EH ? h_col(g, e) : dir(e - C::EH);
+        if (m == 0)
+            return e < C::EH ? h_col(g, e) : -1;
+        if (C::RH == 0)
+            return e < C::EH ? h_col(g, e) : dir(e - C::EH);
+        return e < C::EH || h_col(g, e - C::EH) >= C::RH ? -1 : h_col(g, e - C::EH);
+    }
+    // The weights that entries [e, e + n) of every lane multiply in tile T:
+    // out[lane][j].  (Columns do not depend on the row, but for row 0 of the
+    // output tile, so they are looked up once and not for every weight.)
+    template <int n>
+    static void gather(const std::vector<View> &v, int T, int e, float (&out)[64][n])
+    {
+        for (int g = 0; g < 2; ++g) {
+            int cols[2][n];
+            for (int j = 0; j < n; ++j) {
+                cols[0][j] = tile_col(T, 0, g, e + j);
+                cols[1][j] = tile_col(T, 1, g, e + j);
+            }
+            for (int m = 0; m < 32; ++m) {
+                const float *row = tile_row(v, T, m);
+                const int *col = cols[m > 0];
+                for (int j = 0; j < n; ++j)
+                    out[m + 32 * g][j] = row && col[j] >= 0 ? row[col[j]] : 0.0f;
+            }
         }
-        // output tile: row 0 density (reads h), rows 1..3 colour logits
-        if (m == 0) {
-            const View &S = v[C::D];
-            return e < C::EH ? S.W[h_col(g, e)] : 0.0f;
-        }
-        if (m > 3)
-            return 0.0f;
-        const View &O = v.back();
-        const int c3 = m - 1;
-        if (C::RH > 0) {
-            if (e < C::EH)
-                return 0.0f;
-            const int row = h_col(g, e - C::EH);
-            return row < C::RH ? O.W[(size_t)c3 * O.in + row] : 0.0f;
-        }
-        if (e < C::EH)
-            return O.W[(size_t)c3 * O.in + h_col(g, e)];
-        const int f = d_col(g, e - C::EH);
-        return f < C::DD ? O.W[(size_t)c3 * O.in + C::W + f] : 0.0f;
     }
 
     static float bval(const std::vector<View> &v, int T, int row)
@@ -440,24 +463,32 @@ struct Packer {
     {
         std::vector<View> v;
         views(w, v);
+        if constexpr (C::SPLIT) {
+            Split<C> sp(w, v);
+            sp.pack(stream, block);
+            return;
+        }
         for (int s = 0; s < C::NS; ++s) {
             const int T = C::st_tile(s), c0 = C::st_c0(s);
             unsigned char *base = stream + (size_t)C::st_offset(s) * 1024;
             for (int u = 0; u < C::st_units_pad(s); ++u) {
                 unsigned char *unit = base + (size_t)u * 1024;
-                for (int lane = 0; lane < 64; ++lane) {
-                    const int m = lane % 32, g = lane / 32;
-                    for (int j = 0; j < (C::BF16 ? 8 : 4); ++j) {
-                        // bf16: 8 k-entries of chunk c0 + u; fp32: chunk c0 + 4u + j, one entry
-                        const int e = C::BF16 ? 8 * (c0 + u) + j : c0 + 4 * u + j;
-                        const float val = u < C::st_units(s) ? wval(v, T, m, g, e) : 0.0f;
-                        if (C::BF16) {
-                            const __bf16 bv = (__bf16)val;
-                            __builtin_memcpy(unit + lane * 16 + 2 * j, &bv, 2);
-                        } else {
-                            __builtin_memcpy(unit + lane * 16 + 4 * j, &val, 4);
-                        }
-                    }
+                // bf16: 8 k-entries of chunk c0 + u; fp32: one each of chunks
+                // c0 + 4 u .. + 3
+                constexpr int n = C::BF16 ? 8 : 4;
+                if (u >= C::st_units(s)) {
+                    memset(unit, 0, 1024);
+                    continue;
+                }
+                float x[64][n];
+                gather(v, T, C::BF16 ? 8 * (c0 + u) : c0 + 4 * u, x);
+                if constexpr (C::BF16) {
+                    __bf16 y[64][n];
+                    for (int i = 0; i < 64 * n; ++i)
+                        y[i / n][i % n] = (__bf16)x[i / n][i % n];
+                    memcpy(unit, y, sizeof(y));
+                } else {
+                    memcpy(unit, x, sizeof(x));
                 }
             }
         }
@@ -470,8 +501,233 @@ struct Packer {
     }
 };
 
+// The split form: fp32 heads on the fp16 matrix units.
+//
+// Every fp32 operand a is carried as a_hi = fp16(a) and a_lo = fp16(a - a_hi)
+// (nearest even, 23 significant bits together), every product as a_lo b_hi +
+// a_hi b_lo + a_hi b_hi, accumulated in fp32: three MFMAs of 32x32x16 in 96
+// cycles where the fp32 units take 512.  fp16's exponents are not fp32's, so
+// both operands are kept in its range by powers of two (exact):
+// - weights, here: each hidden unit's row and bias are scaled so that the
+//   row's largest |weight| lies in [1, 2), and the next layers' column of
+//   that unit by the inverse (a ReLU network is unchanged by that); all
+//   weights are then stored times 2^14.  An output row (density, colour) is
+//   scaled alone, its factor kept in the block.
+// - activations, in the kernel: per sample and layer, by 2^(15 - e), where
+//   2^e exceeds (largest row sum of |W|) (largest |input|) + largest |b|, so
+//   that none exceeds 2^15.  What is lost then is below 2^-40 of that bound.
+// Heads whose rows or biases do not fit this (fits()) keep the fp32 units.
+//
+// Bound by the matrix units (power-limited) with 7 VALU instructions per
+// output value beside them; one accumulator per tile (two, for the small and
+// the large products, would cost the 8x128 heads their second wave per SIMD).
+// 9.1 M samples of 8x128 heads: 18.2 ms on the fp32 units (142 TFLOP/s),
+// 5.9 ms here; pixels off the float64 render by 6.9e-6 before, 6.8e-6 now
+// (2.3e-7 and 1.9e-7 for opaque rays): the encoding's rounding, not the
+// products', is what is left.
+template <class C>
+struct Split {
+    typedef Packer<C> Pk;
+    std::vector<float> w;
+    std::vector<typename Pk::View> v;
+    float factor[4];  // output rows: true = stored * factor
+
+    const float *base;
+    bool ok = true;
+
+    // 2^e
+    static float pow2(int e) { return ldexpf(1.0f, e); }
+    // The power of two 2^-e that takes a row's largest |weight| to [1, 2) (1
+    // for a row of zeros); e outside [-40, 40] does not fit.
+    float row_scale(const float *p, int n)
+    {
+        // (magnitudes compare as integers, which the compiler vectorises)
+        unsigned bits = 0;
+        for (int i = 0; i < n; ++i) {
+            unsigned u;
+            memcpy(&u, p + i, 4);
+            u &= 0x7FFFFFFFu;
+            bits = u > bits ? u : bits;
+        }
+        float m;
+        memcpy(&m, &bits, 4);
+        if (m == 0.0f)
+            return 1.0f;
+        int x;
+        (void)frexpf(m, &x);
+        if (x < -39 || x > 41) {
+            ok = false;
+            return 1.0f;
+        }
+        return pow2(1 - x);
+    }
+    float *at(const float *p) { return w.data() + (p - base); }
+    // columns [c0, c0 + col.size()) of a matrix times col, by rows
+    static void scale_columns(float *p, int out, int in, int c0, const std::vector<float> &col)
+    {
+        for (int r = 0; r < out; ++r)
+            for (size_t i = 0; i < col.size(); ++i)
+                p[(size_t)r * in + c0 + i] *= col[i];
+    }
+
+    Split(const float *src, const std::vector<typename Pk::View> &views)
+        : w(src, views.back().b + views.back().out), v(views), base(src)
+    {
+        std::vector<float> col;  // what the unit scales leave for the next layer's columns
+        std::vector<float> mag;  // |biases|
+        float typical = 1.0f;    // about the size of a layer's inputs
+        // a layer's rows to [1, 2); col: the inverse scales
+        auto rows = [&](const typename Pk::View &L) {
+            col.assign(L.out, 1.0f);
+            mag.resize(L.out);
+            float sq = 0.0f;
+            for (int r = 0; r < L.out; ++r) {
+                float *p = at(L.W) + (size_t)r * L.in, *b = at(L.b) + r;
+                const float f = row_scale(p, L.in);
+                *b *= f;
+                mag[r] = fabsf(*b);
+                float part[8] = {};
+                for (int i = 0; i < L.in; ++i)
+                    p[i] *= f;
+                for (int i = 0; i + 8 <= L.in; i += 8)
+                    for (int j = 0; j < 8; ++j)
+                        part[j] += p[i + j] * p[i + j];
+                for (float q : part)
+                    sq += q;
+                col[r] = 1.0f / f;
+            }
+            // one unit must not dwarf the others (all share a sample's scale):
+            // no bias above 2^12 times what the layer's units reach
+            const float top = *std::max_element(mag.begin(), mag.end());
+            std::nth_element(mag.begin(), mag.begin() + L.out / 2, mag.end());
+            typical = 0.5f * sqrtf(sq / L.out) * typical + mag[L.out / 2];
+            if (!(top <= 4096.0f * typical) || !(typical < 0x1p100f))
+                ok = false;
+        };
+        for (int l = 0; l < C::D; ++l) {
+            if (l > 0)
+                scale_columns(at(v[l].W), v[l].out, v[l].in, l == C::SKIP ? C::P : 0, col);
+            rows(v[l]);
+        }
+        scale_columns(at(v[C::D].W), 1, v[C::D].in, 0, col);
+        scale_columns(at(v[C::D + 1].W), v[C::D + 1].out, v[C::D + 1].in, 0, col);
+        if (C::RH > 0) {
+            rows(v[C::D + 1]);
+            scale_columns(at(v.back().W), 3, v.back().in, 0, col);
+        }
+        for (int j = 0; j < 4; ++j) {  // density, colour
+            const typename Pk::View &L = j ? v.back() : v[C::D];
+            float *p = at(L.W) + (size_t)(j ? j - 1 : 0) * L.in;
+            const float f = row_scale(p, L.in);
+            for (int i = 0; i < L.in; ++i)
+                p[i] *= f;
+            factor[j] = 1.0f / f;
+        }
+        for (typename Pk::View &L : v) {
+            L.W = at(L.W);
+            L.b = at(L.b);
+        }
+    }
+
+    // whether a head's weights can take the split form
+    static bool fits(const float *src)
+    {
+        std::vector<typename Pk::View> v;
+        Pk::views(src, v);
+        return Split(src, v).ok;
+    }
+
+    // x (|x| < 65504) to fp16, nearest even, and what is left of it.  In
+    // integers and without a branch, so that the compiler vectorises it: a
+    // host without a conversion instruction calls a routine for each.
+    static inline unsigned short to_f16(float x, float &rest)
+    {
+        unsigned u;
+        memcpy(&u, &x, 4);
+        const unsigned sign = u & 0x80000000u, a = u ^ sign;
+        // normal: drop 13 bits
+        const unsigned h1 = (a + 0xFFFu + ((a >> 13) & 1u) - 0x38000000u) >> 13;
+        const unsigned b1 = (h1 << 13) + 0x38000000u;
+        // below 2^-14: multiples of 2^-24, the spacing of [0.5, 1)
+        float f;
+        memcpy(&f, &a, 4);
+        const float r = f + 0.5f, q = r - 0.5f;
+        unsigned h2, b2;
+        memcpy(&h2, &r, 4);
+        h2 -= 0x3F000000u;
+        memcpy(&b2, &q, 4);
+        const unsigned pick = (int)a >= 0x38800000 ? 0xFFFFFFFFu : 0u;
+        const unsigned h = (h1 & pick) | (h2 & ~pick);
+        const unsigned back = (b1 & pick) | (b2 & ~pick) | sign;
+        float b;
+        memcpy(&b, &back, 4);
+        rest = x - b;
+        return (unsigned short)(h | (sign >> 16));
+    }
+
+    void pack(unsigned char *stream, float *block)
+    {
+        for (int s = 0; s < C::NS; ++s) {
+            const int T = C::st_tile(s), c0 = C::st_c0(s), nu = C::st_units_pad(s);
+            unsigned char *out = stream + (size_t)C::st_offset(s) * 1024;
+            for (int u = 0; u < nu; u += 2) {  // units u (low halves), u + 1 (high halves)
+                if (u >= C::st_units(s)) {
+                    memset(out + (size_t)u * 1024, 0, 2048);
+                    continue;
+                }
+                float x[64][8], y[512], rest[512];
+                Pk::gather(v, T, 8 * (c0 + u / 2), x);
+                memcpy(y, x, sizeof(y));
+                unsigned short h[2][512];
+                for (int i = 0; i < 512; ++i)
+                    h[1][i] = to_f16(0x1p14f * y[i], rest[i]);
+                for (int i = 0; i < 512; ++i) {
+                    float none;
+                    h[0][i] = to_f16(rest[i], none);
+                }
+                memcpy(out + (size_t)u * 1024, h, sizeof(h));
+            }
+        }
+        for (int i = 0; i < C::BLOCK_FLOATS; ++i)
+            block[i] = 0.0f;
+        for (int T = 0; T < C::NT; ++T)
+            for (int g = 0; g < 2; ++g)
+                for (int i = 0; i < 16; ++i)
+                    block[(T * 2 + g) * 16 + i] = Pk::bval(v, T, c_row(g, i));
+        for (int l = 0; l <= C::D; ++l) {
+            if (l == C::D && C::RH == 0)
+                continue;
+            const typename Pk::View &L = v[l == C::D ? C::D + 1 : l];
+            float n1 = 0.0f, b1 = 0.0f;
+            for (int r = 0; r < L.out; ++r) {
+                const float *p = L.W + (size_t)r * L.in;
+                float part[8] = {}, sum = 0.0f;
+                int i = 0;
+                for (; i + 8 <= L.in; i += 8)
+                    for (int j = 0; j < 8; ++j)
+                        part[j] += fabsf(p[i + j]);
+                for (; i < L.in; ++i)
+                    sum += fabsf(p[i]);
+                for (float q : part)
+                    sum += q;
+                n1 = sum > n1 ? sum : n1;
+                b1 = fabsf(L.b[r]) > b1 ? fabsf(L.b[r]) : b1;
+            }
+            // (a little above, for the kernel's own rounding of the bound)
+            block[C::SC_OFF + 2 * l] = 1.001f * n1;
+            block[C::SC_OFF + 2 * l + 1] = 1.001f * b1;
+        }
+        for (int j = 0; j < 4; ++j)
+            block[C::SC_OUT + j] = factor[j];
+    }
+};
+
 // ---------------------------------------------------------------------------
 // Device helpers
+__device__ __forceinline__ f32x16 mfma(const f16x8 &a, const f16x8 &b, const f32x16 &c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+}
 __device__ __forceinline__ f32x16 mfma(const bf16x8 &a, const bf16x8 &b, const f32x16 &c)
 {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
@@ -592,8 +848,40 @@ __device__ __forceinline__ void wait_all() { asm volatile("s_waitcnt vmcnt(0) lg
 // compiler from moving LDS accesses across it.
 __device__ __forceinline__ void wg_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
+// One k-chunk of B: a lane's E entries of a sample's layer input.
+struct SplitChunk {
+    f16x8 hi, lo;
+};
 template <class C>
-using Chunk = std::conditional_t<C::BF16, bf16x8, float>;
+using Chunk = std::conditional_t<C::SPLIT, SplitChunk, std::conditional_t<C::BF16, bf16x8, float>>;
+// an entry of the stored encoding's table
+template <class C>
+using TabEntry = std::conditional_t<C::BF16, bf16x8, float>;
+
+// Entries 2 p, 2 p + 1 of a split chunk: v_cvt_pk_f16_f32 for the high halves
+// (nearest even), one fused multiply-add each for the remainders.
+__device__ __forceinline__ void split_pair(SplitChunk &c, int p, float a, float b)
+{
+    const f16x2 h = __builtin_convertvector(f32x2{a, b}, f16x2);
+    const f16x2 l = __builtin_convertvector(
+        f32x2{fmaf((float)h[0], -1.0f, a), fmaf((float)h[1], -1.0f, b)}, f16x2);
+    c.hi[2 * p] = h[0];
+    c.hi[2 * p + 1] = h[1];
+    c.lo[2 * p] = l[0];
+    c.lo[2 * p + 1] = l[1];
+}
+
+// The value is computed by this point (and not moved past a wait that follows).
+__device__ __forceinline__ void pin(bf16x8 &x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void pin(float &x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void pin(SplitChunk &x) { asm volatile("" : "+v"(x.hi), "+v"(x.lo)); }
+
+// larger of x here and in the other lane group (lane ^ 32)
+__device__ __forceinline__ float half_max(float x)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
 
 // "no tile left" from the work queues
 constexpr unsigned kNoTile = 0xFFFFFFFFu;
@@ -606,13 +894,14 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
     const unsigned *__restrict__ bucket, const unsigned *__restrict__ totals,
     const unsigned *__restrict__ offsets, int num_sites, RenderGeometry geo,
     const float *__restrict__ tbuf, const void *__restrict__ dirbuf,
-    const Chunk<C> *__restrict__ gxtab,
+    const TabEntry<C> *__restrict__ gxtab,
     const unsigned char *__restrict__ streams, const float *__restrict__ blocks,
     float4 *__restrict__ sr, unsigned *__restrict__ queue, HeadMask empty)
 {
     constexpr bool soft = SOFT;
     using CT = Chunk<C>;
-    using AT = std::conditional_t<C::BF16, bf16x8, f32x4>;  // one LDS unit per lane
+    // one LDS unit per lane
+    using AT = std::conditional_t<C::SPLIT, f16x8, std::conditional_t<C::BF16, bf16x8, f32x4>>;
     constexpr int NB = C::NB, NS = C::NS;
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     float *hb = reinterpret_cast<float *>(lds + C::HB_OFF);
@@ -885,6 +1174,18 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
         float xs[NB][3];  // sample positions, kept to re-encode for the skip layer
         unsigned sid[NB], ray[NB];
         bool valid[NB];
+        // split: the layer inputs at hand are the true ones times 2^(15 - ex);
+        // in_max bounds |gamma(x)|, top is the largest of a layer's scaled
+        // outputs so far, mul and add the factors of the layer's accumulators
+        // and biases (see Split)
+        int ex = 0, ex_h = 0;
+        float in_max = 1.0f, top = 0.0f, mul = 0.0f, add = 0.0f;
+        // fp32 entries -> split chunks, scaled
+        auto split_entries = [&](const float *f, auto &out) {
+#pragma unroll
+            for (int e = 0; e < C::EX; e += 2)
+                split_pair(out[e / 8], e % 8 / 2, f[e] * add, f[e + 1] * add);
+        };
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             valid[nb] = (wave * NB + nb) * 32 + n < row_end - row0;
@@ -896,8 +1197,19 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
             ray[nb] = r;
             if constexpr (C::GX) {
                 // this lane group's entries of the sample's row, as stored
-                const Chunk<C> *src = gxtab + ((size_t)sid[nb] * 2 + g) * C::EXC;
-                if constexpr (C::BF16) {
+                const TabEntry<C> *src = gxtab + ((size_t)sid[nb] * 2 + g) * (C::BF16 ? C::EXC : C::EX);
+                if constexpr (C::SPLIT) {
+                    float f[C::EX];
+#pragma unroll
+                    for (int e = 0; e < C::EX; e += 4) {
+                        const f32x4 v = *reinterpret_cast<const f32x4 *>(src + e);
+                        f[e] = v[0]; f[e + 1] = v[1]; f[e + 2] = v[2]; f[e + 3] = v[3];
+                    }
+                    in_max = half_max(fmaxf(1.0f, fmaxf(fabsf(f[0]), fabsf(f[1]))));
+                    ex = __builtin_amdgcn_frexp_expf(in_max);
+                    add = ldexpf(1.0f, 15 - ex);
+                    split_entries(f, gx[nb]);
+                } else if constexpr (C::BF16) {
 #pragma unroll
                     for (int ch = 0; ch < C::EXC; ++ch)
                         gx[nb][ch] = src[ch];
@@ -920,7 +1232,12 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
             xs[nb][2] = x[2];
             float f[C::EX];
             encode_x<C>(x, g, f);
-            if constexpr (C::BF16) {
+            if constexpr (C::SPLIT) {
+                in_max = fmaxf(fmaxf(1.0f, fabsf(x[0])), fmaxf(fabsf(x[1]), fabsf(x[2])));
+                ex = __builtin_amdgcn_frexp_expf(in_max);
+                add = ldexpf(1.0f, 15 - ex);
+                split_entries(f, gx[nb]);
+            } else if constexpr (C::BF16) {
 #pragma unroll
                 for (int ch = 0; ch < C::EXC; ++ch)
                     gx[nb][ch] = to_bf16x8(f + 8 * ch);
@@ -930,6 +1247,14 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
                     gx[nb][e] = f[e];
             }
         }
+        // encoded here, under the latency of what the wait below is for: left
+        // to itself the compiler moves the encoding past the wait (6x64 heads,
+        // 67 M samples: 3.27 -> 3.23 ms)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int ch = 0; ch < C::EXC; ++ch)
+                pin(gx[nb][ch]);
         wait_all();  // weight stages 0..2 and the head block have landed
         if (tid == 0)
             s_q[0] = has_next ? take_rest(q_first) : kNoTile;
@@ -940,14 +1265,17 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
         CT gbuf[NB][C::ERHC > 0 ? C::ERHC : 1];    // colour hidden outputs
         CT gxs[NB][C::EXC];                        // gamma(x) again, for the skip layer
         CT gd[NB][C::EDC];                         // gamma(d)
+        float gdf[C::SPLIT ? C::ED : 1];           // the same as loaded
         f32x16 acc[2][NB];                         // by output-tile parity
-        AT fr[kPrefetch];
+        f32x16 bv;                                 // split: the finished tile's biases
+        AT fr[C::PF];
 
         auto frag = [&](auto sc, int j) -> AT {
             constexpr int s = decltype(sc)::value;
             return *reinterpret_cast<const AT *>(slot(ring + s) + (j * 64 + lane) * 16);
         };
         auto load_bias = [&](auto tc) {
+            // split: into bv, for tile T's epilogue; else as the accumulators of T
             constexpr int T = decltype(tc)::value;
             const float *b = hb + (T * 2 + g) * 16;
             f32x16 v;
@@ -956,9 +1284,36 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
                 const f32x4 q = *reinterpret_cast<const f32x4 *>(b + 4 * j);
                 v[4 * j] = q[0]; v[4 * j + 1] = q[1]; v[4 * j + 2] = q[2]; v[4 * j + 3] = q[3];
             }
+            if constexpr (C::SPLIT) {
+                bv = v;
+                return;
+            }
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
                 acc[T % 2][nb] = v;
+        };
+        // split: the scales of the outputs of layer l (C::D: the colour hidden
+        // layer), whose inputs are complete
+        auto next_scale = [&](auto lc) {
+            constexpr int l = decltype(lc)::value;
+            const float n1 = hb[C::SC_OFF + 2 * l], b1 = hb[C::SC_OFF + 2 * l + 1];
+            float m = l == 0 ? in_max : ldexpf(half_max(top), ex - 15);
+            if constexpr (l > 0 && l == C::SKIP)
+                m = fmaxf(m, in_max);
+            if constexpr (l == C::D) {
+                m = fmaxf(m, 1.0f);
+                ex_h = ex;
+            }
+            float bound = fmaf(n1, m, b1);
+            if constexpr (C::SKIP >= 0 && l + 1 == C::SKIP)
+                bound = fmaxf(bound, in_max);  // the skip layer's gamma(x) takes the same scale
+            if constexpr (l + 1 == C::D)
+                bound = fmaxf(bound, 1.0f);  // and so does gamma(d)
+            const int e = __builtin_amdgcn_frexp_expf(fminf(bound, 0x1p126f));
+            mul = ldexpf(1.0f, ex - e - 14);
+            add = ldexpf(1.0f, 15 - e);
+            ex = e;
+            top = 0.0f;
         };
         // ReLU + conversion of output tile T into the next layer's input chunks,
         // in pieces so that it can be spread over the next tile's MFMAs:
@@ -969,7 +1324,18 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
             constexpr int kind = C::t_kind(T), mt = C::t_mt(T), par = C::t_layer(T) % 2;
             constexpr int nb = p % NB, h = p / NB;
             const f32x16 &a = acc[T % 2][nb];
-            if constexpr (kind != K_OUT) {
+            if constexpr (C::SPLIT) {
+                // values 2 p and 2 p + 1: 7 VALU operations each
+                if constexpr (mt == 0 && p == 0)
+                    next_scale(ic<kind == K_HID ? C::t_layer(T) : C::D>{});
+                const float v0 = fmaxf(fmaf(a[2 * p], mul, bv[2 * p] * add), 0.0f);
+                const float v1 = fmaxf(fmaf(a[2 * p + 1], mul, bv[2 * p + 1] * add), 0.0f);
+                top = fmaxf(top, fmaxf(v0, v1));
+                if constexpr (kind == K_HID)
+                    split_pair(hbuf[par][0][2 * mt + p / 4], p % 4, v0, v1);
+                else
+                    split_pair(gbuf[0][2 * mt + p / 4], p % 4, v0, v1);
+            } else if constexpr (kind != K_OUT) {
                 if constexpr (C::BF16) {
                     if constexpr (kind == K_HID)
                         hbuf[par][nb][2 * mt + h] = relu_bf16(a, h);
@@ -986,14 +1352,15 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
                 }
             }
         };
-        constexpr int NPIECE = C::BF16 ? 2 * NB : 4 * NB;
+        constexpr int NPIECE = C::SPLIT ? 8 : C::BF16 ? 2 * NB : 4 * NB;
 
         // stage 0's bias and the first fragments of the window
-        load_bias(ic<0>{});
-        static_for<0, (kPrefetch < C::FTOTAL ? kPrefetch : C::FTOTAL)>([&](auto fc) {
+        if constexpr (!C::SPLIT)
+            load_bias(ic<0>{});
+        static_for<0, (C::PF < C::FTOTAL ? C::PF : C::FTOTAL)>([&](auto fc) {
             constexpr int F = decltype(fc)::value;
             constexpr int fs = C::f_stage(F), fi = C::f_index(F);
-            fr[F % kPrefetch] = frag(ic<fs>{}, fi);
+            fr[F % C::PF] = frag(ic<fs>{}, fi);
         });
 
         // ---- stages ------------------------------------------------------------
@@ -1043,10 +1410,18 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
                         const f32x4 b1 = *reinterpret_cast<const f32x4 *>(dp + 64 + g * 32 + 16);
                         static_for<0, 4>([&](auto kc) {
                             constexpr int k = decltype(kc)::value;
+                            if constexpr (C::SPLIT) {
+                                gdf[k] = a0[k];
+                                gdf[4 + k] = a1[k];
+                                gdf[8 + k] = b0[k];
+                                gdf[12 + k] = b1[k];
+                                return;
+                            } else {
                             gd[nb][k] = a0[k];
                             gd[nb][4 + k] = a1[k];
                             gd[nb][8 + k] = b0[k];
                             gd[nb][12 + k] = b1[k];
+                            }
                         });
                     }
                 }
@@ -1061,7 +1436,9 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
                 for (int nb = 0; nb < NB; ++nb) {
                     float f[C::EX];
                     encode_x<C>(xs[nb], g, f);
-                    if constexpr (C::BF16) {
+                    if constexpr (C::SPLIT) {
+                        split_entries(f, gxs[nb]);
+                    } else if constexpr (C::BF16) {
 #pragma unroll
                         for (int ch = 0; ch < C::EXC; ++ch)
                             gxs[nb][ch] = to_bf16x8(f + 8 * ch);
@@ -1070,6 +1447,14 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
                         for (int e = 0; e < C::EX; ++e)
                             gxs[nb][e] = f[e];
                     }
+                }
+            }
+
+            if constexpr (C::SPLIT) {
+                if constexpr (s == C::S_GDUSE) {
+#pragma unroll
+                    for (int e = 0; e < C::ED; e += 2)
+                        split_pair(gd[0][e / 8], e % 8 / 2, gdf[e] * add, gdf[e + 1] * add);
                 }
             }
 
@@ -1096,14 +1481,21 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
             };
 
             // Schedule of one step j: a piece of the previous tile's epilogue
-            // (first stage of a tile), the read of the fragment kPrefetch
+            // (first stage of a tile), the read of the fragment PF
             // ahead (possibly the next stage's), the next tile's bias (late in
             // its last stage), then this step's MFMAs; sched_barrier keeps the
             // order, so LDS latency hides behind the MFMAs in between.
             constexpr bool EPI = first && T > 0;
-            constexpr int ESTEPS = EPI ? (NF < NPIECE ? NF : NPIECE) : 0;
+            // (split: done before the step that reads the last chunk they fill:
+            // the eighth unit of a tile at the earliest, two per chunk)
+            constexpr int EMAX = C::SPLIT && NPIECE > 6 ? 6 : NPIECE;
+            constexpr int ESTEPS = EPI ? (NF < EMAX ? NF : EMAX) : 0;
+            static_assert(!C::SPLIT || !EPI || kind != K_HID || C::t_mt(T) > 0 ||
+                              2 * (C::EHC - 2 + (layer == C::SKIP ? C::EXC : 0)) + 2 >= ESTEPS,
+                          "a chunk is read before its epilogue");
             constexpr int JB0 = NF >= 2 ? NF - 2 : 0;
             constexpr int JB = next_first ? (JB0 > ESTEPS ? JB0 : ESTEPS) : NF;  // bias step
+            constexpr int bias_tile = C::SPLIT ? T : next_tile;
             static_for<0, NF>([&](auto jc) {
                 constexpr int j = decltype(jc)::value;
                 constexpr int F = C::foff(s) + j;
@@ -1115,14 +1507,25 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
                             epilogue_piece(ic<T - 1>{}, pc);
                     });
                 }
-                const AT a = fr[F % kPrefetch];
-                if constexpr (F + kPrefetch < C::FTOTAL) {
-                    constexpr int fs = C::f_stage(F + kPrefetch), fi = C::f_index(F + kPrefetch);
-                    fr[F % kPrefetch] = frag(ic<fs>{}, fi);
+                const AT a = fr[F % C::PF];
+                if constexpr (F + C::PF < C::FTOTAL) {
+                    constexpr int fs = C::f_stage(F + C::PF), fi = C::f_index(F + C::PF);
+                    fr[F % C::PF] = frag(ic<fs>{}, fi);
                 }
                 if constexpr (j == JB && next_first)
-                    load_bias(ic<next_tile>{});
-                if constexpr (C::BF16) {
+                    load_bias(ic<bias_tile>{});
+                if constexpr (C::SPLIT) {
+                    const SplitChunk x = in_chunk(ic<c0 + j / 2>{}, 0);
+                    if constexpr (j % 2 == 0) {  // the weights' low halves
+                        if constexpr (first && j == 0)
+                            acc[T % 2][0] = mfma(a, x.hi, f32x16{});
+                        else
+                            acc[T % 2][0] = mfma(a, x.hi, acc[T % 2][0]);
+                    } else {
+                        acc[T % 2][0] = mfma(a, x.lo, acc[T % 2][0]);
+                        acc[T % 2][0] = mfma(a, x.hi, acc[T % 2][0]);
+                    }
+                } else if constexpr (C::BF16) {
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb)
                         acc[T % 2][nb] = mfma(a, in_chunk(ic<c0 + j>{}, nb), acc[T % 2][nb]);
@@ -1137,14 +1540,23 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
                 __builtin_amdgcn_sched_barrier(0);
             });
             if constexpr (JB >= NF && next_first)
-                load_bias(ic<next_tile>{});
+                load_bias(ic<bias_tile>{});
         });
 
         // ---- density and colour: rows 0..3 of the output tile, lanes g = 0 ----
         constexpr int TO = C::NT - 1;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-            const f32x16 &a = acc[TO % 2][nb];
+            f32x16 a = acc[TO % 2][nb];
+            if constexpr (C::SPLIT) {
+                // the rows' biases and factors; the colours read the colour
+                // hidden layer's outputs, where there is one
+                const float sh = ldexpf(1.0f, (C::RH > 0 ? ex_h : ex) - 29);
+                const float sc = ldexpf(1.0f, ex - 29);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    a[j] = fmaf(a[j] * (j ? sc : sh), hb[C::SC_OUT + j], hb[TO * 32 + j]);
+            }
             if (g == 0 && valid[nb])
                 sr[soft ? row0 + (wave * NB + nb) * 32 + n : sid[nb]] =
                     make_float4(fmaxf(a[0], 0.0f), sigmoid(a[1]), sigmoid(a[2]), sigmoid(a[3]));
@@ -1169,7 +1581,7 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
 template <class C>
 __global__ __launch_bounds__(256) void gx_encode_kernel(RenderGeometry geo,
                                                         const float *__restrict__ tbuf,
-                                                        Chunk<C> *__restrict__ out)
+                                                        TabEntry<C> *__restrict__ out)
 {
     typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
     constexpr int U = C::EX * (C::BF16 ? 2 : 4) / 16;  // 16-byte units per row
@@ -1227,7 +1639,7 @@ hipError_t launch_gx_encode(const RenderGeometry &g, const float *t, void *gxtab
     const unsigned long long lanes = 2ull * g.num_samples;
     const unsigned long long want = (lanes + 255) / 256, cap = (unsigned long long)cus * 64;
     gx_encode_kernel<C><<<(unsigned)(want < cap ? want : cap), 256, 0, s>>>(
-        g, t, reinterpret_cast<Chunk<C> *>(gxtab));
+        g, t, reinterpret_cast<TabEntry<C> *>(gxtab));
     return hipGetLastError();
 }
 
@@ -1254,7 +1666,7 @@ hipError_t launch_mlp(const unsigned *bucket, const unsigned *totals, const unsi
         return true;
     }();
     (void)raised;
-    const Chunk<C> *gx = reinterpret_cast<const Chunk<C> *>(gxtab);
+    const TabEntry<C> *gx = reinterpret_cast<const TabEntry<C> *>(gxtab);
     // as many persistent workgroups as fit, but no more than there can be
     // tiles (each head's last one may be partial)
     const unsigned long long heads_rows = soft ? num_sites : 1;
@@ -1281,10 +1693,20 @@ hipError_t launch_mlp(const unsigned *bucket, const unsigned *totals, const unsi
 
 // The stored-encoding form of an architecture without a skip layer.
 template <class C>
-using StoredForm = Cfg<C::BF16, C::W, C::D, C::SKIP, C::RH, C::LP, true>;
+using StoredForm = Cfg<C::PREC, C::W, C::D, C::SKIP, C::RH, C::LP, true>;
 
 template <class C>
-const MlpVariant *variant()
+constexpr auto split_fits() -> bool (*)(const float *)
+{
+    if constexpr (C::SPLIT && !C::GX)
+        return &Split<C>::fits;
+    else
+        return nullptr;
+}
+
+// plain: the form for weights that do not fit this one (split only)
+template <class C>
+const MlpVariant *variant(const MlpVariant *plain = nullptr)
 {
     const MlpVariant *stored = nullptr;
     if constexpr (C::SKIP < 0 && !C::GX) {
@@ -1301,7 +1723,9 @@ const MlpVariant *variant()
                                  stored,
                                  C::GX ? (size_t)2 * C::EX * (C::BF16 ? 2 : 4) : 0,
                                  C::LP,
-                                 C::GX ? &launch_gx_encode<C> : nullptr};
+                                 C::GX ? &launch_gx_encode<C> : nullptr,
+                                 plain,
+                                 split_fits<C>()};
     return &v;
 }
 

@@ -1,4 +1,4 @@
-"""The grouped MLP's tile queues at the edges of their range."""
+"""The grouped MLP's tile queues and its float32 form, at the edges of their ranges."""
 import numpy as np
 import pytest
 
@@ -46,4 +46,92 @@ def test_every_tile_is_taken_once(tiles, heads):
         torch.cuda.synchronize()
         for x, y in zip(whole, part):
             assert torch.equal(x[a:b], y)
+    r.close()
+
+
+def _units(arch, w, pick, factor):
+    """w with hidden unit pick(l) of every layer l scaled by factor: rows and
+    biases times it, the columns that read the unit by its inverse."""
+    w = w.copy()
+    v = scenes.weight_views(arch, w)
+    for l in range(arch.depth):
+        u = pick(l)
+        W, b = v["hidden%d" % l]
+        W[u] *= factor
+        b[u] *= factor
+        if l + 1 < arch.depth:
+            nxt = v["hidden%d" % (l + 1)][0]
+            nxt[:, (arch.pos_dim if l + 1 == arch.skip_layer else 0) + u] /= factor
+        else:
+            v["sigma"][0][:, u] /= factor
+            v["rgb_hidden" if arch.rgb_hidden else "rgb_out"][0][:, u] /= factor
+    return w
+
+
+def _head(arch, kind, seed):
+    """One head's weights (biases included) whose rows' magnitudes the float32
+    form has to bring into fp16's range, or refuse."""
+    rng = np.random.Generator(np.random.PCG64(seed))
+    w = scenes.make_weights(arch, 1, seed, 1.0)[0]
+    v = scenes.weight_views(arch, w)
+    for tag in v:
+        v[tag][1][:] += rng.normal(0.0, 0.05, len(v[tag][1])).astype(np.float32)
+    if kind == "small_units":
+        w = _units(arch, w, lambda l: np.arange(0, arch.width, 3), np.float32(2.0 ** -14))
+    elif kind == "large_units":
+        w = _units(arch, w, lambda l: np.array([l, l + 7]), np.float32(2.0 ** 17))
+    elif kind == "dead":
+        for l in range(arch.depth):
+            v["hidden%d" % l][0][l::5] = 0.0
+            v["hidden%d" % l][1][l::5] = 0.0
+        v["rgb_out"][0][1] = 0.0
+    elif kind == "tiny_row":  # does not fit: a row of 2^-60
+        v["hidden1"][0][3] *= np.float32(2.0 ** -60)
+    elif kind == "huge_bias":  # does not fit: one unit far above the others
+        v["hidden1"][1][3] = 1e6
+        v["hidden2"][0][:, 3] = 0.0
+    return w
+
+
+@pytest.mark.parametrize("arch", [scenes.ARCH_TINY, scenes.ARCH_SMALL, scenes.ARCH_128],
+                         ids=["4x64", "6x64", "8x128"])
+@pytest.mark.parametrize("kind", ["plain", "small_units", "large_units", "dead", "tiny_row",
+                                  "huge_bias"])
+def test_float32_heads_of_any_scale(arch, kind):
+    """float32 heads against the float64 oracle, at the float32 bar of 1e-4:
+    weights that the split form scales into range and weights that it leaves
+    to the fp32 units; rays up to 40 units from the origin (37 of them: the
+    last tile is partial)."""
+    import oracle
+    from paper_2011_12490_amd import derf
+    heads, n = 3, 29
+    w = np.stack([_head(arch, kind if k == 1 else "plain", 40 + k) for k in range(heads)])
+    sites = scenes.make_sites("uniform", heads)
+    o, d = _rays(37, seed=8)
+    o[::5] *= 40.0
+    ref = oracle.render(sites, arch, w, o, d, 0.0, 1.0, n, 0, seed=6)
+    r = derf.Renderer(sites, arch, w, "fp32")
+    got = r.render(torch.from_numpy(o).cuda(), torch.from_numpy(d).cuda(), 0.0, 1.0, n, seed=6)
+    torch.cuda.synchronize()
+    r.close()
+    for x, y in zip(got, (ref.rgb, ref.depth, ref.opacity)):
+        assert np.abs(x.cpu().numpy() - y).max() <= 1e-4
+
+
+@pytest.mark.parametrize("arch", [scenes.ARCH_TINY, scenes.ARCH_128], ids=["4x64", "8x128"])
+def test_float32_split_ignores_its_neighbours(arch):
+    """Rays of NaN, infinite and huge origins leave the other rays' outputs
+    bitwise as they are without them (scales are per sample)."""
+    from paper_2011_12490_amd import derf
+    sites = scenes.make_sites("uniform", 2)
+    r = derf.Renderer(sites, arch, scenes.make_weights(arch, 2, sigma_bias=1.0), "fp32")
+    o, d = _rays(40)
+    bad = o.copy()
+    bad[3], bad[11, 1], bad[12], bad[25] = np.nan, np.inf, 1e30, -3e38
+    a, b = (r.render(torch.from_numpy(x).cuda(), torch.from_numpy(d).cuda(), 0.0, 1.0, 33, seed=2)
+            for x in (o, bad))
+    torch.cuda.synchronize()
+    keep = [i for i in range(40) if i not in (3, 11, 12, 25)]
+    for x, y in zip(a, b):
+        assert torch.equal(x[keep], y[keep])
     r.close()
