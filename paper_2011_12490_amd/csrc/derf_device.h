@@ -21,8 +21,11 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint2 k)
             k.x += 0x9E3779B9u;
             k.y += 0xBB67AE85u;
         }
-        const unsigned lo0 = 0xD2511F53u * c.x, hi0 = __umulhi(0xD2511F53u, c.x);
-        const unsigned lo1 = 0xCD9E8D57u * c.z, hi1 = __umulhi(0xCD9E8D57u, c.z);
+        // one v_mad_u64_u32 per product: the 32-bit multiplies run at a
+        // quarter of the rate, and a low and a high one take two
+        const uint64_t p0 = (uint64_t)0xD2511F53u * c.x, p1 = (uint64_t)0xCD9E8D57u * c.z;
+        const unsigned lo0 = (unsigned)p0, hi0 = (unsigned)(p0 >> 32);
+        const unsigned lo1 = (unsigned)p1, hi1 = (unsigned)(p1 >> 32);
         c = make_uint4(hi1 ^ c.y ^ k.x, lo1, hi0 ^ c.w ^ k.y, lo0);
     }
     return c;

@@ -29,9 +29,11 @@ struct HeadMask {
 constexpr int kMaxSeg = 32;
 constexpr int kMaxCand = 11;
 struct alignas(16) SegRec {
-    float t_end;          // the segment covers depths up to t_end
-    unsigned char ncand;  // candidate sites, ascending
-    unsigned char cand[kMaxCand];
+    float t_end;             // the segment covers depths up to t_end
+    // low four bits: candidate sites; high four bits, if not 0: no site comes
+    // near the segment's own between 2^-high of its length from either end
+    unsigned char ncand_safe;
+    unsigned char cand[kMaxCand];  // the segment's own site, then the others, ascending
 };
 // Heads from which the assignment uses the walk instead of all sites (below,
 // the search over all sites costs less than the walk and its table lookups).

@@ -206,6 +206,15 @@ __device__ __forceinline__ unsigned long long group_or(unsigned long long x)
     return x;
 }
 
+template <int L>
+__device__ __forceinline__ float group_max(float x)
+{
+    group_steps<L>([&](auto ctrl) {
+        x = fmaxf(x, __uint_as_float(dpp_u32<decltype(ctrl)::value>(__float_as_uint(x))));
+    });
+    return x;
+}
+
 // sum of x over the lanes of the group below this one (gl: lane in group)
 template <int L>
 __device__ __forceinline__ unsigned group_exclusive_sum(unsigned x, int gl)
@@ -236,22 +245,28 @@ __device__ __forceinline__ unsigned group_exclusive_sum(unsigned x, int gl)
 // site's cell.  Each move strictly increases d.phi of the current site, so a
 // ray takes at most K segments and never returns to a cell.
 //
-// Each segment keeps, in ascending order, c and every site j with
+// Each segment keeps c and, in ascending order, every other site j with
 // min(f_j(t0), f_j(t1)) <= tau at its ends t0, t1 (tau = 1e-4 (1 + the
 // squared distances to c there)).  f_j is linear, so a site left out is
 // farther than c by more than tau on the whole segment -- far above the
 // float32 rounding of the squared distances (a few ulp) -- and can neither
 // be the float32 nearest site of a sample in the segment nor tie with it:
 // the float32 argmin over the segment's candidates is the float32 argmin over
-// all sites, whatever crossing ends the segment.  A ray with more than
-// kMaxSeg segments, or a segment with more than kMaxCand candidates, is
-// marked (nseg = 0) for the search over all sites.
+// all sites, whatever crossing ends the segment.  The same linear f_j is
+// at most tau only on the fraction (tau - min) / (max - min) of the segment at
+// its smaller end; between the largest such fractions at both ends c alone
+// can be nearest, and the lookup takes it without looking at the sites (the
+// fraction is rounded up to a power of two, kept in four bits).  A ray with more than
+// kMaxSeg segments, a segment with more than kMaxCand candidates or
+// coordinates beyond float32's squares is marked (nseg = 0) for the search
+// over all sites.
 //
-// One lane per ray (the largest frames) asks for 8 waves per SIMD: 64
-// registers without spills, against 96 and 5 waves by default, to cover the
-// lanes' differing walk lengths.  The grouped forms would spill at 64.
+// One lane per ray (the largest frames) asks for 7 waves per SIMD: 72
+// registers without spills, against 5 waves by default, to cover the lanes'
+// differing walk lengths (8 waves would spill).  The grouped forms take what
+// they need.
 template <int L>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(L == 1 ? 8 : 1)))
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(L == 1 ? 7 : 1)))
 void ray_walk_kernel(RenderGeometry g, const float4 *__restrict__ sites, int num_sites,
                      SegRec *__restrict__ seg, unsigned char *__restrict__ nseg)
 {
@@ -298,8 +313,11 @@ void ray_walk_kernel(RenderGeometry g, const float4 *__restrict__ sites, int num
     }
     SegRec *out = seg + (size_t)r * kMaxSeg;
     int ns = 0;
-    bool ok = true;
-    for (;;) {
+    // a ray that leaves float32's range (or is not a number) has no nearest
+    // site in float32: the search over all sites says which it takes
+    bool ok = fabs(x0) + fabs(y0) + fabs(z0) + fabs(ox + g.far_t * dx) + fabs(oy + g.far_t * dy) +
+                  fabs(oz + g.far_t * dz) < 1e18;
+    while (ok) {
         const double qc0 = q(x0, y0, z0, c), bc = dproj(c);
         // the first crossing: smallest f_j(t0) / (-slope_j) over slope_j < 0,
         // f_j = q_j - q_c, slope_j = 2 d.(phi_c - phi_j)
@@ -330,14 +348,19 @@ void ray_walk_kernel(RenderGeometry g, const float4 *__restrict__ sites, int num
         const double dc0 = fma(x0, x0, fma(y0, y0, z0 * z0)) + qc0;
         const double dc1 = fma(x1, x1, fma(y1, y1, z1 * z1)) + qc1;
         const double tau = 1e-4 * (1.0 + fmax(dc0, dc1));
-        // this lane's candidates, ascending, as a byte string (at most 12 kept)
+        // this lane's candidates but c, ascending, as a byte string (at most
+        // 12 kept), and the largest fraction that one of them is near on
         unsigned long long lo = 0, hi = 0;
         unsigned cl = 0;
+        float part = 0x1p-16f;
         for (int j = j0; j < j1; ++j) {
-            bool take = j == c;
-            if (!take)
-                take = fmin(q(x0, y0, z0, j) - qc0, q(x1, y1, z1, j) - qc1) <= tau;
-            if (take) {
+            if (j == c)
+                continue;
+            const double f0 = q(x0, y0, z0, j) - qc0, f1 = q(x1, y1, z1, j) - qc1;
+            const double fm = fmin(f0, f1);
+            if (fm <= tau) {
+                part = fmaxf(part, ((float)(tau - fm) + 1e-30f) *
+                                       (1.01f * __builtin_amdgcn_rcpf((float)fabs(f1 - f0))));
                 if (cl < 8)
                     lo |= (unsigned long long)j << (8 * cl);
                 else if (cl < 12)
@@ -345,13 +368,15 @@ void ray_walk_kernel(RenderGeometry g, const float4 *__restrict__ sites, int num
                 cl = min(cl + 1, 12u);
             }
         }
-        const unsigned nc = group_sum<L>(cl);
+        const unsigned nc = group_sum<L>(cl) + 1;
+        part = group_max<L>(part);
         if (nc > (unsigned)kMaxCand || ns == kMaxSeg) {
             ok = false;
             break;
         }
-        // the group's list in lane order (ascending sites), after the count byte
-        const int k = 8 * (int)(group_exclusive_sum<L>(cl, gl) + 1);
+        // the group's list in lane order (ascending sites), after the count
+        // byte and c
+        const int k = 8 * (int)(group_exclusive_sum<L>(cl, gl) + 2);
         if (k >= 64) {
             hi = lo << (k - 64);
             lo = 0;
@@ -363,8 +388,12 @@ void ray_walk_kernel(RenderGeometry g, const float4 *__restrict__ sites, int num
         hi = group_or<L>(hi);
         if (gl == 0) {
             const float te = nextc < 0 ? INFINITY : (float)t1;
-            *reinterpret_cast<uint4 *>(out + ns) = make_uint4(
-                __float_as_uint(te), (unsigned)lo | nc, (unsigned)(lo >> 32), (unsigned)hi);
+            // 2^-safe >= part (infinite or NaN: 0)
+            const int e = part < 1.0f ? __builtin_amdgcn_frexp_expf(part) : 0;
+            const unsigned safe = e < 0 ? (unsigned)min(-e, 15) : 0u;
+            *reinterpret_cast<uint4 *>(out + ns) =
+                make_uint4(__float_as_uint(te), (unsigned)lo | nc | (safe << 4) | ((unsigned)c << 8),
+                           (unsigned)(lo >> 32), (unsigned)hi);
         }
         ++ns;
         if (nextc < 0)
@@ -380,11 +409,16 @@ void ray_walk_kernel(RenderGeometry g, const float4 *__restrict__ sites, int num
 }
 
 // Owning cell of a sample at x (depth t): through its ray's walk table tab
-// of ns segments (the float32 nearest among the segment's candidates,
-// ascending), or, with ns == 0, over all sites.
+// of ns segments over [near_t, far_t] (the segment's own site inside its safe
+// stretch, else the float32 nearest among its candidates, the lowest of equal
+// ones), or, with ns == 0, over all sites.  Every segment has candidates (the
+// sites of the cells before and after it at least), but few samples lie where
+// they matter, so most steps of a wave skip their distances: the lookup of
+// 2^28 samples, 64 skewed sites, 959 -> 784 us.  What bounds it now is the
+// bisection and the Philox rounds.
 __device__ __forceinline__ unsigned nearest_site(const float4 *s_sites, int num_sites,
-                                                 const SegRec *tab, unsigned ns, float t,
-                                                 float x, float y, float z)
+                                                 const SegRec *tab, unsigned ns, float near_t,
+                                                 float far_t, float t, float x, float y, float z)
 {
     float best = INFINITY;
     unsigned bk = 0;
@@ -392,14 +426,21 @@ __device__ __forceinline__ unsigned nearest_site(const float4 *s_sites, int num_
         const float4 p = s_sites[k];
         const float ex = x - p.x, ey = y - p.y, ez = z - p.z;
         const float d2 = fmaf(ez, ez, fmaf(ey, ey, ex * ex));
-        if (d2 < best) {
+        if (d2 < best || (d2 == best && k < bk)) {
             best = d2;
             bk = k;
         }
     };
     if (ns == 0) {
-        for (int k = 0; k < num_sites; ++k)
-            consider(k);
+        for (int k = 0; k < num_sites; ++k) {
+            const float4 p = s_sites[k];
+            const float ex = x - p.x, ey = y - p.y, ez = z - p.z;
+            const float d2 = fmaf(ez, ez, fmaf(ey, ey, ex * ex));
+            if (d2 < best) {
+                best = d2;
+                bk = k;
+            }
+        }
         return bk;
     }
     // the first segment whose end is >= t (the last one's end is +inf)
@@ -412,7 +453,13 @@ __device__ __forceinline__ unsigned nearest_site(const float4 *s_sites, int num_
             lo = mid + 1;
     }
     const uint4 rec = *reinterpret_cast<const uint4 *>(tab + lo);
-    const unsigned nc = rec.y & 0xFFu;
+    const unsigned nc = rec.y & 15u, safe = (rec.y >> 4) & 15u;
+    const float t0 = lo > 0 ? tab[lo - 1].t_end : near_t;
+    const float t1 = fminf(__uint_as_float(rec.x), far_t);
+    const float edge = (t1 - t0) * __uint_as_float((127u - safe) << 23);
+    bk = (rec.y >> 8) & 0xFFu;
+    if (safe > 0 && t - t0 >= edge && t1 - t >= edge)
+        return bk;
     const unsigned words[3] = {rec.y, rec.z, rec.w};
 #pragma unroll
     for (unsigned q = 0; q < (unsigned)kMaxCand; ++q)
@@ -482,11 +529,11 @@ void sample_assign_kernel(
         if constexpr (WALK) {
             if (staged)
                 return nearest_site(s_sites, num_sites, s_seg + (r - r_first) * kMaxSeg,
-                                    s_nseg[r - r_first], t, x, y, z);
+                                    s_nseg[r - r_first], g.near_t, g.far_t, t, x, y, z);
             return nearest_site(s_sites, num_sites, walk.seg + (size_t)r * kMaxSeg,
-                                walk.nseg[r], t, x, y, z);
+                                walk.nseg[r], g.near_t, g.far_t, t, x, y, z);
         } else {
-            return nearest_site(s_sites, num_sites, nullptr, 0u, t, x, y, z);
+            return nearest_site(s_sites, num_sites, nullptr, 0u, 0.0f, 0.0f, t, x, y, z);
         }
     };
 
