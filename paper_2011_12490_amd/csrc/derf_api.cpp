@@ -186,9 +186,9 @@ struct derf_handle {
 namespace {
 
 // assignment blocks of S samples (S up to 2^32 - 1: the sum is taken in 64 bits)
-inline unsigned blocks_of(unsigned S)
+inline unsigned blocks_of(unsigned S, unsigned block = kBucketBlock)
 {
-    return (unsigned)(((unsigned long long)S + kBucketBlock - 1) / kBucketBlock);
+    return (unsigned)(((unsigned long long)S + block - 1) / block);
 }
 inline unsigned blocks_of_ll(unsigned long long n)
 {
@@ -438,11 +438,21 @@ int render_impl(derf_handle *h, const float *rays_o, const float *rays_d, long l
     const bool hier = samp->n_fine > 0;
     const unsigned R = (unsigned)num_rays, N = (unsigned)samp->n_coarse, NF = (unsigned)samp->n_fine;
     const unsigned S = R * N, Sf = R * NF;
-    const unsigned nblk = blocks_of(S);
-    const unsigned nblk_f = blocks_of(Sf);
-    const unsigned nblk_max = nblk > nblk_f ? nblk : nblk_f;
-    const size_t need =
-        layout(nullptr, S, Sf, R, nblk_max, h->num_sites, h->bf16, h->gx_bytes, nullptr);
+    unsigned block = bucket_block(S), block_f = bucket_block(Sf);
+    unsigned nblk, nblk_f, nblk_max;
+    size_t need;
+    auto plan = [&]() {
+        nblk = blocks_of(S, block);
+        nblk_f = blocks_of(Sf, block_f);
+        nblk_max = nblk > nblk_f ? nblk : nblk_f;
+        need = layout(nullptr, S, Sf, R, nblk_max, h->num_sites, h->bf16, h->gx_bytes, nullptr);
+    };
+    plan();
+    if (fixed_ws && need > fixed_bytes) {
+        // the shorter counts of the large blocks may still fit
+        block = block_f = kBucketBlock;
+        plan();
+    }
     int rc = DERF_OK;
     if (fixed_ws) {
         if (need > fixed_bytes)
@@ -486,16 +496,25 @@ int render_impl(derf_handle *h, const float *rays_o, const float *rays_d, long l
     };
     // assignment counts -> bucket -> per-head MLP of one pass
     auto bucket_and_mlp = [&](int pass, const RenderGeometry &gp, const float *t,
-                              const uint8_t *cell, unsigned nb, unsigned *totals,
+                              const uint8_t *cell, unsigned nb, unsigned blk, unsigned *totals,
                               float4 *sr) -> int {
+        // short counts are scanned by the scatter (the scan stage is empty then)
+        const bool one = (unsigned long long)nb * h->num_sites <= kScanInScatter;
         HIP_TRY(mark(pass, DERF_STAGE_BUCKET_SCAN, 0), "hipEventRecord");
-        HIP_TRY(launch_bucket_scan(b.counts, nb, h->num_sites, totals, b.mlp_queue, s),
-                "bucket_scan launch");
+        if (!one)
+            HIP_TRY(launch_bucket_scan(b.counts, nb, h->num_sites, totals, b.mlp_queue, s),
+                    "bucket_scan launch");
         HIP_TRY(mark(pass, DERF_STAGE_BUCKET_SCAN, 1), "hipEventRecord");
         HIP_TRY(mark(pass, DERF_STAGE_BUCKET_SCATTER, 0), "hipEventRecord");
-        HIP_TRY(launch_bucket_scatter(cell, b.counts, totals, gp.num_samples, nb, h->num_sites,
-                                      h->empty, b.bucket, sr, s),
-                "bucket_scatter launch");
+        if (one)
+            HIP_TRY(launch_bucket_scan_scatter(cell, b.counts, totals, b.mlp_queue,
+                                               gp.num_samples, nb, blk, h->num_sites, h->empty,
+                                               b.bucket, sr, s),
+                    "bucket_scan_scatter launch");
+        else
+            HIP_TRY(launch_bucket_scatter(cell, b.counts, totals, gp.num_samples, nb, blk,
+                                          h->num_sites, h->empty, b.bucket, sr, s),
+                    "bucket_scatter launch");
         HIP_TRY(mark(pass, DERF_STAGE_BUCKET_SCATTER, 1), "hipEventRecord");
         HIP_TRY(mark(pass, DERF_STAGE_MLP, 0), "hipEventRecord");
         HIP_TRY(launch_groups(h, b.bucket, totals, gp, t, b.dirbuf, sr, b.mlp_queue, false, s,
@@ -507,19 +526,18 @@ int render_impl(derf_handle *h, const float *rays_o, const float *rays_d, long l
 
     // ---- single or coarse pass: stratified samples (Sec. 3.1)
     HIP_TRY(mark(0, DERF_STAGE_SAMPLE, 0), "hipEventRecord");
-    HIP_TRY(launch_ray_encode(g, b.dirbuf, h->bf16, s), "ray_encode launch");
     const WalkTable walk{b.walk_seg, b.walk_nseg};
     if (walk.seg)
         HIP_TRY(launch_ray_walk(g, h->sites, h->num_sites, b.walk_seg, b.walk_nseg, s),
                 "ray_walk launch");
-    HIP_TRY(launch_sample_assign(g, h->sites, h->num_sites, walk, b.t, b.cell,
-                                 b.counts, nblk, s),
+    HIP_TRY(launch_sample_assign(g, h->sites, h->num_sites, walk, b.t, b.cell, b.counts, nblk,
+                                 block, DirOut{b.dirbuf, h->bf16}, s),
             "sample_assign launch");
     if (b.gxtab)
         HIP_TRY(h->groups[0].mlp->stored->encode(g, b.t, b.gxtab, h->mlp_grid, s),
                 "gx_encode launch");
     HIP_TRY(mark(0, DERF_STAGE_SAMPLE, 1), "hipEventRecord");
-    rc = bucket_and_mlp(0, g, b.t, b.cell, nblk, b.totals, b.sr);
+    rc = bucket_and_mlp(0, g, b.t, b.cell, nblk, block, b.totals, b.sr);
     if (rc != DERF_OK)
         return rc;
     const bool want_dbg = dbg && (dbg->cell || dbg->t || dbg->sigma || dbg->rgb);
@@ -544,13 +562,14 @@ int render_impl(derf_handle *h, const float *rays_o, const float *rays_d, long l
         gf.inv_n = 1.0 / (double)NF;
         HIP_TRY(mark(1, DERF_STAGE_SAMPLE, 0), "hipEventRecord");
         HIP_TRY(launch_assign_given(gf, h->sites, h->num_sites, walk, b.t_fine,
-                                    b.cell_fine, b.counts, nblk_f, s),
+                                    b.cell_fine, b.counts, nblk_f, block_f, s),
                 "assign launch");
         if (b.gxtab)
             HIP_TRY(h->groups[0].mlp->stored->encode(gf, b.t_fine, b.gxtab, h->mlp_grid, s),
                     "gx_encode launch");
         HIP_TRY(mark(1, DERF_STAGE_SAMPLE, 1), "hipEventRecord");
-        rc = bucket_and_mlp(1, gf, b.t_fine, b.cell_fine, nblk_f, b.totals_fine, b.sr_fine);
+        rc = bucket_and_mlp(1, gf, b.t_fine, b.cell_fine, nblk_f, block_f, b.totals_fine,
+                            b.sr_fine);
         if (rc != DERF_OK)
             return rc;
         HIP_TRY(mark(1, DERF_STAGE_COMPOSITE, 0), "hipEventRecord");
@@ -609,7 +628,7 @@ int render_soft_impl(derf_handle *h, const float *rays_o, const float *rays_d,
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     HIP_TRY(hipSetDevice(h->device), "hipSetDevice");
     const unsigned R = (unsigned)num_rays, N = (unsigned)samp->n_coarse, S = R * N;
-    const unsigned nblk = blocks_of(S);
+    const unsigned block = bucket_block(S), nblk = blocks_of(S, block);
     int rc = ensure_workspace(h, layout_soft(nullptr, S, R, nblk, h->num_sites, h->bf16, nullptr));
     if (rc != DERF_OK)
         return rc;
@@ -643,9 +662,8 @@ int render_soft_impl(derf_handle *h, const float *rays_o, const float *rays_d,
     };
     // stratified depths (the owning cells it also writes are not used)
     HIP_TRY(mark(DERF_STAGE_SAMPLE, 0), "hipEventRecord");
-    HIP_TRY(launch_ray_encode(g, b.dirbuf, h->bf16, s), "ray_encode launch");
     HIP_TRY(launch_sample_assign(g, h->sites, h->num_sites, WalkTable{nullptr, nullptr},
-                                 b.t, b.cell, b.counts, nblk, s),
+                                 b.t, b.cell, b.counts, nblk, block, DirOut{b.dirbuf, h->bf16}, s),
             "sample_assign launch");
     HIP_TRY(launch_soft_setup(S, h->num_sites, b.bucket, b.totals, b.mlp_queue, s),
             "soft_setup launch");
@@ -807,7 +825,8 @@ int render_culled_impl(derf_handle *h, const float *rays_o, const float *rays_d,
         return hipEventRecord(h->ev[ev_index(0, stage, end)], s);
     };
     HIP_TRY(mark(DERF_STAGE_SAMPLE, 0), "hipEventRecord");
-    HIP_TRY(launch_ray_encode(g, b.dirbuf, h->bf16, s), "ray_encode launch");
+    if (gated)
+        HIP_TRY(launch_ray_encode(g, b.dirbuf, h->bf16, s), "ray_encode launch");
     // the gated assignment draws the depths itself and needs no nearest site
     const WalkTable walk{gated ? nullptr : b.walk_seg, gated ? nullptr : b.walk_nseg};
     if (gated) {
@@ -818,8 +837,8 @@ int render_culled_impl(derf_handle *h, const float *rays_o, const float *rays_d,
         if (walk.seg)
             HIP_TRY(launch_ray_walk(g, h->sites, K, b.walk_seg, b.walk_nseg, s),
                     "ray_walk launch");
-        HIP_TRY(launch_sample_assign(g, h->sites, K, walk, b.t, b.cell, b.counts,
-                                     nblk, s),
+        HIP_TRY(launch_sample_assign(g, h->sites, K, walk, b.t, b.cell, b.counts, nblk,
+                                     kBucketBlock, DirOut{b.dirbuf, h->bf16}, s),
                 "sample_assign launch");
     }
     HIP_TRY(launch_level_bounds(b.cell, N, R, L, P, c.lb, c.lvl, s),

@@ -10,6 +10,20 @@ namespace derf {
 // Samples covered by one bucketing block: the counting pass and the scatter
 // pass must agree on this partition of the sample range.
 constexpr int kBucketBlock = 4096;
+// The same for frames of at most kSmallFrame samples: a block of 4096 leaves
+// most of the chip idle there (1,024 rays of 192 samples are 48 blocks), and
+// each block takes four rounds one after another.  Above, 4096 keeps the
+// counts (and their scan) a quarter as long.  196,608 samples of 16 heads:
+// assignment and scatter 15.2 + 9.4 us in blocks of 4096.
+constexpr int kSmallBlock = 1024;
+constexpr unsigned kSmallFrame = 1u << 20;
+inline unsigned bucket_block(unsigned num_samples)
+{
+    return num_samples <= kSmallFrame ? (unsigned)kSmallBlock : (unsigned)kBucketBlock;
+}
+// (head, block) counts up to which the scatter scans them itself, each of its
+// blocks reading all (32 KB); above, by a launch of its own.
+constexpr unsigned long long kScanInScatter = 8192;
 // Padded length of the per-ray direction feature vector gamma(d / |d|).
 constexpr int kDirPad = 32;
 constexpr int kMaxSites = 256;
@@ -76,27 +90,43 @@ hipError_t launch_gate(const RenderGeometry &g, const unsigned char *packed, int
 // p[0 .. count) = v (a kernel: no memset node in a captured stream)
 hipError_t launch_fill_u32(unsigned *p, unsigned count, unsigned v, hipStream_t s);
 hipError_t launch_ray_encode(const RenderGeometry &g, void *dirbuf, bool bf16, hipStream_t s);
+// Where launch_sample_assign also writes the rays' direction features (as
+// launch_ray_encode does, by blocks of its own beside the assignment's): one
+// launch instead of two.
+struct DirOut {
+    void *buf;  // null: not here
+    bool bf16;
+};
 // Walk every ray of g through the cells on [near, far] (one lane per ray).
 hipError_t launch_ray_walk(const RenderGeometry &g, const float4 *sites, int num_sites,
                            SegRec *seg, unsigned char *nseg, hipStream_t s);
 // walk: the table of launch_ray_walk for the same rays, or {nullptr, nullptr}
+// block: samples per block of the counts (kBucketBlock or kSmallBlock)
 hipError_t launch_sample_assign(const RenderGeometry &g, const float4 *sites, int num_sites,
                                 const WalkTable &walk, float *t, uint8_t *cell,
-                                unsigned *counts, unsigned num_blocks, hipStream_t s);
+                                unsigned *counts, unsigned num_blocks, unsigned block,
+                                const DirOut &dir, hipStream_t s);
 // same, for given depths t (read only): no sampling
 hipError_t launch_assign_given(const RenderGeometry &g, const float4 *sites, int num_sites,
                                const WalkTable &walk, const float *t,
                                uint8_t *cell, unsigned *counts, unsigned num_blocks,
-                               hipStream_t s);
+                               unsigned block, hipStream_t s);
 // also clears the kMlpQueues tile counters of the MLP launch that follows
 hipError_t launch_bucket_scan(unsigned *counts, unsigned num_blocks, int num_sites,
                               unsigned *totals, unsigned *mlp_queue, hipStream_t s);
 // Samples of 0-capacity heads also get sr = 0 here (the MLP skips those heads).
 hipError_t launch_bucket_scatter(const uint8_t *cell, const unsigned *counts,
                                  const unsigned *totals, unsigned num_samples,
-                                 unsigned num_blocks, int num_sites,
+                                 unsigned num_blocks, unsigned block, int num_sites,
                                  const HeadMask &empty, unsigned *bucket, float4 *sr,
                                  hipStream_t s);
+// launch_bucket_scan and launch_bucket_scatter in one launch, for at most
+// kScanInScatter counts (which stay as they are).
+hipError_t launch_bucket_scan_scatter(const uint8_t *cell, const unsigned *counts,
+                                      unsigned *totals, unsigned *mlp_queue,
+                                      unsigned num_samples, unsigned num_blocks, unsigned block,
+                                      int num_sites, const HeadMask &empty, unsigned *bucket,
+                                      float4 *sr, hipStream_t s);
 // Soft decomposition: bucket[i] = i (i < S), totals[k] = S, queue cleared.
 hipError_t launch_soft_setup(unsigned S, int num_sites, unsigned *bucket, unsigned *totals,
                              unsigned *queue, hipStream_t s);

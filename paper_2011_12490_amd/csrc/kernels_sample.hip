@@ -44,10 +44,9 @@ __device__ __forceinline__ void sincos_pi_pow2(float p, int l, float &s, float &
 // Per-ray direction features: f = [gamma_4(d / |d|) (27 values), 0 x 5],
 // stored as bf16 (round to nearest even) or float.
 template <bool BF16>
-__global__ __launch_bounds__(kThreads) void ray_encode_kernel(const float *__restrict__ rays_d,
-                                                              unsigned num_rays, void *dirbuf)
+__device__ __forceinline__ void ray_encode(const float *__restrict__ rays_d, unsigned num_rays,
+                                           unsigned r, void *dirbuf)
 {
-    const unsigned r = blockIdx.x * kThreads + threadIdx.x;
     if (r >= num_rays)
         return;
     const float dx = rays_d[3 * r], dy = rays_d[3 * r + 1], dz = rays_d[3 * r + 2];
@@ -87,6 +86,13 @@ __global__ __launch_bounds__(kThreads) void ray_encode_kernel(const float *__res
         for (int q = 0; q < kDirPad / 4; ++q)
             out[q] = make_float4(f[4 * q], f[4 * q + 1], f[4 * q + 2], f[4 * q + 3]);
     }
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(kThreads) void ray_encode_kernel(const float *__restrict__ rays_d,
+                                                              unsigned num_rays, void *dirbuf)
+{
+    ray_encode<BF16>(rays_d, num_rays, blockIdx.x * kThreads + threadIdx.x, dirbuf);
 }
 
 // ---------------------------------------------------------------------------
@@ -470,7 +476,9 @@ __device__ __forceinline__ unsigned nearest_site(const float4 *s_sites, int num_
 
 // Stratified depths t, owning cell (nearest site, ties to the lowest index)
 // and per-block head histograms.  Block b covers samples
-// [b * kBucketBlock, (b + 1) * kBucketBlock); each thread takes 4 consecutive
+// [b * BLOCK, (b + 1) * BLOCK), BLOCK = kBucketBlock or kSmallBlock; the
+// blocks past num_blocks, where there are any, write the rays' direction
+// features instead (dir).  Each thread takes 4 consecutive
 // samples per round, so one Philox block serves 4 samples of a ray.  With
 // FROM_T the depths are given (t is read, not written): the assignment of
 // the inverse-CDF samples of hierarchical sampling.  WALK: the owning cell
@@ -478,13 +486,23 @@ __device__ __forceinline__ unsigned nearest_site(const float4 *s_sites, int num_
 // as the search over all sites.  The lookup waits on its table reads, so
 // WALK asks for 8 waves per SIMD (at most 64 registers, no spills; the
 // staging below keeps 8 blocks within the CU's LDS).
-template <bool FROM_T, bool WALK>
+template <bool FROM_T, bool WALK, int BLOCK>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WALK ? 8 : 1)))
 void sample_assign_kernel(
     RenderGeometry g, const float4 *__restrict__ sites, int num_sites,
     WalkTable walk, float *__restrict__ t_out, uint8_t *__restrict__ cell_out,
-    unsigned *__restrict__ counts, unsigned num_blocks)
+    unsigned *__restrict__ counts, unsigned num_blocks, DirOut dir)
 {
+    if constexpr (!FROM_T) {
+        if (blockIdx.x >= num_blocks) {
+            const unsigned r = (blockIdx.x - num_blocks) * kThreads + threadIdx.x;
+            if (dir.bf16)
+                ray_encode<true>(g.rays_d, g.num_rays, r, dir.buf);
+            else
+                ray_encode<false>(g.rays_d, g.num_rays, r, dir.buf);
+            return;
+        }
+    }
     __shared__ float4 s_sites[kMaxSites];
     __shared__ unsigned s_hist[kMaxSites];
     // walk tables of the block's rays, when they are few enough (n >= ~152):
@@ -496,14 +514,14 @@ void sample_assign_kernel(
         s_sites[k] = sites[k];
         s_hist[k] = 0;
     }
-    const unsigned block_base = blockIdx.x * (unsigned)kBucketBlock;
+    const unsigned block_base = blockIdx.x * (unsigned)BLOCK;
     unsigned r_first = 0;
     bool staged = false;
     if constexpr (WALK) {
         unsigned i_;
         unsigned r_last;
         split_sample(block_base, g.n, g.inv_n, r_first, i_);
-        split_sample((unsigned)(min((unsigned long long)block_base + kBucketBlock,
+        split_sample((unsigned)(min((unsigned long long)block_base + BLOCK,
                                     (unsigned long long)g.num_samples) - 1),
                      g.n, g.inv_n, r_last, i_);
         staged = r_last - r_first < (unsigned)kStageRays;
@@ -539,7 +557,7 @@ void sample_assign_kernel(
 
     const uint2 key = make_uint2((unsigned)g.seed, (unsigned)(g.seed >> 32));
     const uint64_t lane_bit = 1ull << (threadIdx.x & 63);
-    for (int round = 0; round < kBucketBlock / (4 * kThreads); ++round) {
+    for (int round = 0; round < BLOCK / (4 * kThreads); ++round) {
         const unsigned s0 = block_base + round * (4 * kThreads) + 4 * threadIdx.x;
         unsigned r, i;
         split_sample(s0 < g.num_samples ? s0 : 0, g.n, g.inv_n, r, i);
@@ -753,6 +771,74 @@ __device__ __forceinline__ void head_block_base(const unsigned *__restrict__ pre
         if (k < num_sites)
             s_base[k] = acc + pre[j];
         acc += tot[j];
+    }
+}
+
+// The same from the unscanned counts (at most kScanInScatter of them), for
+// frames whose counts each block can read whole: wave w sums heads w, w + 4,
+// .. over the blocks, four at a time, all their loads in flight.  Block 0 also
+// writes the totals and clears the tile counters of the MLP that follows.
+__device__ __forceinline__ void head_block_base_scan(const unsigned *__restrict__ counts,
+                                                     unsigned num_blocks, int num_sites,
+                                                     unsigned *s_base, unsigned *s_total,
+                                                     unsigned *__restrict__ totals,
+                                                     unsigned *__restrict__ mlp_queue)
+{
+    constexpr int W = kThreads / 64;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (int k0 = w; k0 < num_sites; k0 += 4 * W) {
+        unsigned tot[4] = {}, pre[4] = {};
+        for (unsigned b = lane; b < num_blocks; b += 64)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int k = k0 + j * W;
+                const unsigned c = k < num_sites ? counts[(size_t)k * num_blocks + b] : 0u;
+                tot[j] += c;
+                pre[j] += b < blockIdx.x ? c : 0u;
+            }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                tot[j] += __shfl_xor(tot[j], off);
+                pre[j] += __shfl_xor(pre[j], off);
+            }
+        if (lane < 4 && k0 + lane * W < num_sites) {
+            // (selected without indexing the registers)
+            s_total[k0 + lane * W] = lane == 0 ? tot[0] : lane == 1 ? tot[1] : lane == 2 ? tot[2] : tot[3];
+            s_base[k0 + lane * W] = lane == 0 ? pre[0] : lane == 1 ? pre[1] : lane == 2 ? pre[2] : pre[3];
+        }
+    }
+    __syncthreads();
+    if (blockIdx.x == 0) {
+        for (int k = threadIdx.x; k < num_sites; k += kThreads)
+            totals[k] = s_total[k];
+        if (threadIdx.x < (unsigned)(kMlpQueues * kMaxHeadGroups))
+            mlp_queue[threadIdx.x] = 0;
+    }
+    if (threadIdx.x >= 64)
+        return;
+    unsigned t[4], sum = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int k = 4 * lane + j;
+        t[j] = k < num_sites ? s_total[k] : 0u;
+        sum += t[j];
+    }
+    unsigned incl = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned y = __shfl_up(incl, off);
+        if (lane >= off)
+            incl += y;
+    }
+    unsigned acc = incl - sum;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int k = 4 * lane + j;
+        if (k < num_sites)
+            s_base[k] += acc;
+        acc += t[j];
     }
 }
 
@@ -1070,25 +1156,32 @@ __global__ __launch_bounds__(kThreads) void level_ray_scatter_kernel(
 // 0-capacity head keeps its bucket slot (the offsets are the same) but gets
 // zero density and colour in sr: the MLP does not evaluate that head.
 // MODE: the key (kCellKey, kCellAtLevel, kLevelCell); num_sites counts the
-// keys.
-template <int MODE>
+// keys.  BLOCK: samples per block (kBucketBlock or kSmallBlock).  SCAN: prefix
+// holds the counts themselves, and the kernel scans them (totals and mlp_queue
+// are outputs then).
+template <int MODE, int BLOCK = kBucketBlock, bool SCAN = false>
 __global__ __launch_bounds__(kThreads) void bucket_scatter_kernel(
     const uint8_t *__restrict__ cell, const unsigned *__restrict__ prefix,
-    const unsigned *__restrict__ totals, unsigned num_samples, unsigned num_blocks,
+    unsigned *__restrict__ totals, unsigned num_samples, unsigned num_blocks,
     int num_sites, HeadMask empty, LevelLive live, unsigned *__restrict__ bucket,
-    float4 *__restrict__ sr)
+    float4 *__restrict__ sr, unsigned *__restrict__ mlp_queue)
 {
     constexpr bool LEVEL = MODE == kCellAtLevel;
     constexpr int kWavesPerBlock = kThreads / 64;
-    constexpr int kSteps = kBucketBlock / kThreads;  // 64-sample steps per wave
+    constexpr int kSteps = BLOCK / kThreads;  // 64-sample steps per wave
     __shared__ unsigned s_base[kMaxSites];
     __shared__ unsigned s_pos[kWavesPerBlock][kMaxSites];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    head_block_base(prefix, totals, num_blocks, num_sites, s_base);
+    if constexpr (SCAN) {
+        head_block_base_scan(prefix, num_blocks, num_sites, s_base, s_pos[0], totals, mlp_queue);
+        __syncthreads();  // s_pos[0] held the totals
+    } else {
+        head_block_base(prefix, totals, num_blocks, num_sites, s_base);
+    }
     for (int k = threadIdx.x; k < num_sites; k += kThreads)
         for (int v = 0; v < kWavesPerBlock; ++v)
             s_pos[v][k] = 0;
-    const unsigned wbase = blockIdx.x * (unsigned)kBucketBlock + w * (kSteps * 64);
+    const unsigned wbase = blockIdx.x * (unsigned)BLOCK + w * (kSteps * 64);
     unsigned cs[kSteps];
     bool in[kSteps];  // the sample exists (LEVEL: and is live at this level)
     wave_bytes(cell, wbase, num_samples, cs);
@@ -1502,30 +1595,37 @@ hipError_t launch_ray_walk(const RenderGeometry &g, const float4 *sites, int num
 
 hipError_t launch_sample_assign(const RenderGeometry &g, const float4 *sites, int num_sites,
                                 const WalkTable &walk, float *t, uint8_t *cell,
-                                unsigned *counts, unsigned num_blocks, hipStream_t s)
+                                unsigned *counts, unsigned num_blocks, unsigned block,
+                                const DirOut &dir, hipStream_t s)
 {
-    if (walk.seg)
-        sample_assign_kernel<false, true><<<num_blocks, kThreads, 0, s>>>(
-            g, sites, num_sites, walk, t, cell, counts, num_blocks);
-    else
-        sample_assign_kernel<false, false><<<num_blocks, kThreads, 0, s>>>(
-            g, sites, num_sites, walk, t, cell, counts, num_blocks);
-    return hipGetLastError();
+    const unsigned grid = num_blocks + (dir.buf ? blocks_for(g.num_rays, kThreads) : 0u);
+    auto go = [&](auto kernel) {
+        kernel<<<grid, kThreads, 0, s>>>(g, sites, num_sites, walk, t, cell, counts, num_blocks, dir);
+        return hipGetLastError();
+    };
+    if (block == (unsigned)kSmallBlock)
+        return walk.seg ? go(sample_assign_kernel<false, true, kSmallBlock>)
+                        : go(sample_assign_kernel<false, false, kSmallBlock>);
+    return walk.seg ? go(sample_assign_kernel<false, true, kBucketBlock>)
+                    : go(sample_assign_kernel<false, false, kBucketBlock>);
 }
 
 hipError_t launch_assign_given(const RenderGeometry &g, const float4 *sites, int num_sites,
                                const WalkTable &walk, const float *t,
                                uint8_t *cell, unsigned *counts, unsigned num_blocks,
-                               hipStream_t s)
+                               unsigned block, hipStream_t s)
 {
     // t is only read in these instantiations
-    if (walk.seg)
-        sample_assign_kernel<true, true><<<num_blocks, kThreads, 0, s>>>(
-            g, sites, num_sites, walk, const_cast<float *>(t), cell, counts, num_blocks);
-    else
-        sample_assign_kernel<true, false><<<num_blocks, kThreads, 0, s>>>(
-            g, sites, num_sites, walk, const_cast<float *>(t), cell, counts, num_blocks);
-    return hipGetLastError();
+    auto go = [&](auto kernel) {
+        kernel<<<num_blocks, kThreads, 0, s>>>(g, sites, num_sites, walk, const_cast<float *>(t),
+                                               cell, counts, num_blocks, DirOut{nullptr, false});
+        return hipGetLastError();
+    };
+    if (block == (unsigned)kSmallBlock)
+        return walk.seg ? go(sample_assign_kernel<true, true, kSmallBlock>)
+                        : go(sample_assign_kernel<true, false, kSmallBlock>);
+    return walk.seg ? go(sample_assign_kernel<true, true, kBucketBlock>)
+                    : go(sample_assign_kernel<true, false, kBucketBlock>);
 }
 
 hipError_t launch_bucket_scan(unsigned *counts, unsigned num_blocks, int num_sites,
@@ -1537,14 +1637,36 @@ hipError_t launch_bucket_scan(unsigned *counts, unsigned num_blocks, int num_sit
 
 hipError_t launch_bucket_scatter(const uint8_t *cell, const unsigned *counts,
                                  const unsigned *totals, unsigned num_samples,
-                                 unsigned num_blocks, int num_sites,
+                                 unsigned num_blocks, unsigned block, int num_sites,
                                  const HeadMask &empty, unsigned *bucket, float4 *sr,
                                  hipStream_t s)
 {
-    bucket_scatter_kernel<kCellKey><<<num_blocks, kThreads, 0, s>>>(
-        cell, counts, totals, num_samples, num_blocks, num_sites, empty, LevelLive{},
-        bucket, sr);
-    return hipGetLastError();
+    auto go = [&](auto kernel) {
+        kernel<<<num_blocks, kThreads, 0, s>>>(cell, counts, const_cast<unsigned *>(totals),
+                                               num_samples, num_blocks, num_sites, empty,
+                                               LevelLive{}, bucket, sr, nullptr);
+        return hipGetLastError();
+    };
+    return block == (unsigned)kSmallBlock ? go(bucket_scatter_kernel<kCellKey, kSmallBlock>)
+                                          : go(bucket_scatter_kernel<kCellKey>);
+}
+
+hipError_t launch_bucket_scan_scatter(const uint8_t *cell, const unsigned *counts,
+                                      unsigned *totals, unsigned *mlp_queue,
+                                      unsigned num_samples, unsigned num_blocks, unsigned block,
+                                      int num_sites, const HeadMask &empty, unsigned *bucket,
+                                      float4 *sr, hipStream_t s)
+{
+    if ((unsigned long long)num_blocks * num_sites > kScanInScatter)
+        return hipErrorInvalidValue;
+    auto go = [&](auto kernel) {
+        kernel<<<num_blocks, kThreads, 0, s>>>(cell, counts, totals, num_samples, num_blocks,
+                                               num_sites, empty, LevelLive{}, bucket, sr, mlp_queue);
+        return hipGetLastError();
+    };
+    return block == (unsigned)kSmallBlock
+               ? go(bucket_scatter_kernel<kCellKey, kSmallBlock, true>)
+               : go(bucket_scatter_kernel<kCellKey, kBucketBlock, true>);
 }
 
 hipError_t launch_composite(const RenderGeometry &g, const float *t, const uint8_t *cell,
@@ -1631,7 +1753,7 @@ hipError_t launch_level_head_order(const RenderGeometry &g, unsigned levels, int
     if (e != hipSuccess)
         return e;
     bucket_scatter_kernel<kLevelCell><<<num_blocks, kThreads, 0, s>>>(
-        cell, counts, totals, g.num_samples, num_blocks, keys, empty, lk, order, sr);
+        cell, counts, totals, g.num_samples, num_blocks, keys, empty, lk, order, sr, nullptr);
     e = hipGetLastError();
     if (e != hipSuccess)
         return e;
@@ -1659,8 +1781,8 @@ hipError_t launch_level_scatter(const RenderGeometry &g, const uint8_t *cell,
                                 float4 *sr, hipStream_t s)
 {
     bucket_scatter_kernel<kCellAtLevel><<<num_blocks, kThreads, 0, s>>>(
-        cell, counts, totals, g.num_samples, num_blocks, num_sites, empty,
-        level_live(lv), bucket, sr);
+        cell, counts, const_cast<unsigned *>(totals), g.num_samples, num_blocks, num_sites, empty,
+        level_live(lv), bucket, sr, nullptr);
     return hipGetLastError();
 }
 
