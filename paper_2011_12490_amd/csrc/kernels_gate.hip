@@ -32,6 +32,7 @@
 // walk nor the nearest-site search.
 #pragma clang fp contract(off)
 
+#include <type_traits>
 #include <string.h>
 
 #include "derf_device.h"
@@ -264,12 +265,20 @@ __global__ __launch_bounds__(kGateThreads) void gate_kernel(RenderGeometry g,
                 acc = mfma(ah, hl[c], acc);
                 acc = mfma(ah, hh[c], acc);
             }
+            auto rows = [&](auto first) {  // accumulators 8 first .. 8 first + 7
+                constexpr int f = decltype(first)::value;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const bool take = acc[r] > best;
-                best = take ? acc[r] : best;
-                bk = take ? 32 * mt2 + acc_row(lg, r) : bk;
-            }
+                for (int r = 8 * f; r < 8 * f + 8; ++r) {
+                    const bool take = acc[r] > best;
+                    best = take ? acc[r] : best;
+                    bk = take ? 32 * mt2 + acc_row(lg, r) : bk;
+                }
+            };
+            rows(std::integral_constant<int, 0>{});
+            // the tile's upper 16 rows, where there are heads among them (3
+            // VALU instructions a row: 48 of 727 per 64 samples at 16 heads)
+            if (32 * mt2 + 16 < num_sites)
+                rows(std::integral_constant<int, 1>{});
         }
         // the other lane group holds the other rows of the same sample
         const float ob = __shfl_xor(best, 32);

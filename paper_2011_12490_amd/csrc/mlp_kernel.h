@@ -105,9 +105,10 @@ struct Cfg {
     static constexpr int NB = BF16 ? 2 : 1;    // 32-sample column blocks per wave
     static constexpr int WAVES = 4;
     static constexpr int THREADS = WAVES * 64;
-    // 64-wide bf16 heads: three workgroups per CU (4 KB ring slots, at most
-    // 168 VGPRs), so that more waves hide the per-tile gathers and encoding
-    static constexpr int WG_PER_CU = W >= 256 ? 1 : (BF16 && W == 64 ? 3 : 2);
+    // 64-wide heads but on the fp32 units: three workgroups per CU (4 KB ring
+    // slots, at most 168 VGPRs), so that more waves hide the per-tile gathers
+    // and encoding (split, 16.8 M samples of 6x64: 3.04 -> 2.92 ms)
+    static constexpr int WG_PER_CU = W >= 256 ? 1 : (PREC != P_F32 && W == 64 ? 3 : 2);
     static constexpr int TILE = WAVES * NB * 32;
     static constexpr int P = 3 + 6 * LP;       // gamma(x) length
     static constexpr int DD = 27;              // gamma(d) length (4 frequencies)
@@ -119,7 +120,7 @@ struct Cfg {
     static constexpr int MTR = (RH + 31) / 32; // output tiles of the colour hidden layer
     static constexpr int ERH = MTR * 16;       // colour-hidden entries per lane
     static constexpr int EXC = EX / E, EHC = EH / E, EDC = ED / E, ERHC = ERH / E;
-    static constexpr int UMAX = BF16 && W == 64 ? 4 : 8;  // units per stage
+    static constexpr int UMAX = PREC != P_F32 && W == 64 ? 4 : 8;  // units per stage
     static constexpr int CMAX = UMAX * CPU / UPC;  // chunks per stage
     static constexpr int NBUF = 8;             // LDS ring slots (power of two)
     static constexpr int G = 2;                // stages per barrier
