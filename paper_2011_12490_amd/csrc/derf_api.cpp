@@ -190,10 +190,6 @@ inline unsigned blocks_of(unsigned S, unsigned block = kBucketBlock)
 {
     return (unsigned)(((unsigned long long)S + block - 1) / block);
 }
-inline unsigned blocks_of_ll(unsigned long long n)
-{
-    return (unsigned)((n + kBucketBlock - 1) / kBucketBlock);
-}
 
 template <class T>
 T *carve(char *&p, size_t count)
@@ -863,11 +859,11 @@ int render_culled_impl(derf_handle *h, const float *rays_o, const float *rays_d,
             const unsigned *src = c.order;
             if (l > 0) {
                 // a level that is one piece holds at most P samples of each ray
-                const unsigned lblk =
-                    P > 0 && l + 1 < L ? std::min(nblk, blocks_of_ll((unsigned long long)R * P))
-                                       : nblk;
+                const unsigned long long most =
+                    P > 0 && l + 1 < L ? std::min((unsigned long long)S, (unsigned long long)R * P)
+                                       : S;
                 HIP_TRY(launch_level_compact(g, l, L, K, c.order, c.key_offsets,
-                                             c.key_totals, c.lvl, b.cell, lblk, tot, b.bucket,
+                                             c.key_totals, c.lvl, b.cell, most, tot, b.bucket,
                                              b.mlp_queue, s),
                         "level_compact launch");
                 src = b.bucket;

@@ -46,13 +46,13 @@ hipError_t launch_level_head_order(const RenderGeometry &g, unsigned levels, int
 // Level l >= 1 after the one-pass bucketing: copies the level's entries whose
 // ray is still open from order to the same stretches of bucket, each head's
 // packed at the front of its stretch, and counts them in live [K] (zero on
-// entry).  num_blocks blocks of 4096 entries must cover the level.  Clears
-// the MLP's tile counters.
+// entry).  max_entries bounds the level's entries.  Clears the MLP's tile
+// counters.
 hipError_t launch_level_compact(const RenderGeometry &g, unsigned level, unsigned levels,
                                 int heads, const unsigned *order,
                                 const unsigned *offsets, const unsigned *totals,
-                                const uint8_t *lvl, const uint8_t *cell, unsigned num_blocks,
-                                unsigned *live, unsigned *bucket, unsigned *mlp_queue,
+                                const uint8_t *lvl, const uint8_t *cell,
+                                unsigned long long max_entries, unsigned *live, unsigned *bucket, unsigned *mlp_queue,
                                 hipStream_t s);
 // A level below the last, bucketed ray by ray (each open ray's samples at
 // such a level are one run of one cell, touching at most two blocks): the

@@ -7,6 +7,7 @@
 // run and in every reference.
 #pragma clang fp contract(off)
 
+#include <algorithm>
 #include <type_traits>
 
 #include "derf_device.h"
@@ -1283,82 +1284,98 @@ __global__ __launch_bounds__(kThreads) void level_head_init_kernel(
 // same positions of bucket, each head's live ones (their ray still open)
 // packed at the front of the head's stretch; live[k] counts them.  Wave w of
 // block b takes 1024 consecutive entries in 16 steps of 64: pass 1 counts
-// them per head (equal-head ballots), one atomic per head and wave reserves
-// their positions, pass 2 ranks and writes.  The order of the waves' pieces
+// them per head (equal-head runs), one atomic per head and block reserves
+// their positions, pass 2 ranks and writes.  The order of the blocks' pieces
 // within a head is not fixed; each sample's outputs do not depend on it.
 // Block 0 clears the MLP's tile counters.
-__global__ __launch_bounds__(kThreads) void level_compact_kernel(
+//
+// The atomics all meet in one cache line (16 heads) and are served one after
+// another, about 10 ns each, so a block is as large as it can be: 16 waves,
+// 16,384 entries.  4.6 M entries of 16 heads: 70 us with an atomic per wave
+// and head, 32 us so.
+constexpr int kCompactThreads = 1024;
+constexpr unsigned kCompactBlock = 16384;
+__global__ __launch_bounds__(kCompactThreads) void level_compact_kernel(
     const unsigned *__restrict__ order, const unsigned *__restrict__ offsets,
     const unsigned *__restrict__ totals, const uint8_t *__restrict__ lvl,
     const uint8_t *__restrict__ cell, unsigned level, unsigned levels, int heads,
     unsigned num_samples, unsigned *__restrict__ live, unsigned *__restrict__ bucket,
     unsigned *__restrict__ mlp_queue)
 {
-    constexpr int kWavesPerBlock = kThreads / 64;
-    constexpr int kSteps = kBucketBlock / kThreads;
+    constexpr int kWavesPerBlock = kCompactThreads / 64;
+    constexpr int kSteps = kCompactBlock / kCompactThreads;
     __shared__ unsigned s_pos[kWavesPerBlock][kMaxSites];
     if (blockIdx.x == 0 && threadIdx.x < (unsigned)(kMlpQueues * kMaxHeadGroups))
         mlp_queue[threadIdx.x] = 0;
     const unsigned begin = offsets[level * heads];
     const unsigned end = level + 1 < levels ? offsets[(level + 1) * heads] : num_samples;
-    if ((unsigned long long)blockIdx.x * kBucketBlock >= end - begin)
-        return;  // (block-uniform) past the level's entries
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (int k = lane; k < heads; k += 64)
-        s_pos[w][k] = 0;
-    const unsigned wbase = begin + blockIdx.x * (unsigned)kBucketBlock + w * (kSteps * 64);
-    unsigned sid[kSteps], cs[kSteps];
-    bool ok[kSteps];
+    // (block-uniform; the last level's entries are only bounded by all samples,
+    // so the grid is not sized for the bound)
+    for (unsigned long long blk = blockIdx.x; blk * kCompactBlock < end - begin; blk += gridDim.x) {
+        for (int k = lane; k < heads; k += 64)
+            s_pos[w][k] = 0;
+        const unsigned long long wbase = begin + blk * kCompactBlock + w * (kSteps * 64);
+        unsigned sid[kSteps], cs[kSteps];
+        bool ok[kSteps];
 #pragma unroll
-    for (int step = 0; step < kSteps; ++step) {
-        const unsigned j = wbase + step * 64 + lane;
-        const bool in = j < end;
-        sid[step] = in ? order[j] : 0u;
-    }
-#pragma unroll
-    for (int step = 0; step < kSteps; ++step) {
-        const unsigned j = wbase + step * 64 + lane;
-        const bool in = j < end;
-        cs[step] = in ? cell[sid[step]] : 0u;
-        ok[step] = in && lvl[sid[step]] == level;
-    }
-    __syncthreads();
-    // pass 1: this wave's live entries per head (run leaders)
-#pragma unroll
-    for (int step = 0; step < kSteps; ++step) {
-        const uint64_t any = __ballot(ok[step]);
-        if (any == 0)
-            continue;
-        const LaneRuns r = lane_runs(cs[step], ok[step], any);
-        if ((r.starts >> lane) & 1ull)
-            atomicAdd(&s_pos[w][cs[step]], r.len);
-    }
-    __syncthreads();
-    // reserve each head's positions
-    for (int k = lane; k < heads; k += 64) {
-        const unsigned cnt = s_pos[w][k];
-        s_pos[w][k] = cnt ? atomicAdd(live + k, cnt) : 0u;
-    }
-    __syncthreads();
-    // pass 2: ranks and writes
-#pragma unroll
-    for (int step = 0; step < kSteps; ++step) {
-        const uint64_t any = __ballot(ok[step]);
-        if (any == 0)
-            continue;
-        const unsigned c = cs[step];
-        const LaneRuns r = lane_runs(c, ok[step], any);
-        unsigned start = 0;
-        if ((r.starts >> lane) & 1ull)
-            start = atomicAdd(&s_pos[w][c], r.len);
-        start = __shfl(start, r.first);
-        if (ok[step]) {
-            const unsigned rank = start + (unsigned)(lane - r.first);
-            const unsigned pos = offsets[level * heads + c] + rank;
-            // within the head's stretch whenever the totals are consistent
-            if (rank < totals[level * heads + c] && pos < num_samples)
-                bucket[pos] = sid[step];
+        for (int step = 0; step < kSteps; ++step) {
+            const unsigned long long j = wbase + step * 64 + lane;
+            const bool in = j < end;
+            sid[step] = in ? order[j] : 0u;
         }
+#pragma unroll
+        for (int step = 0; step < kSteps; ++step) {
+            const bool in = wbase + step * 64 + lane < end;
+            cs[step] = in ? cell[sid[step]] : 0u;
+            ok[step] = in && lvl[sid[step]] == level;
+        }
+        __syncthreads();
+        // pass 1: this wave's live entries per head (run leaders)
+#pragma unroll
+        for (int step = 0; step < kSteps; ++step) {
+            const uint64_t any = __ballot(ok[step]);
+            if (any == 0)
+                continue;
+            const LaneRuns r = lane_runs(cs[step], ok[step], any);
+            if ((r.starts >> lane) & 1ull)
+                atomicAdd(&s_pos[w][cs[step]], r.len);
+        }
+        __syncthreads();
+        // reserve each head's positions, the waves' pieces in order
+        for (int k = threadIdx.x; k < heads; k += kCompactThreads) {
+            unsigned sum = 0;
+            for (int v = 0; v < kWavesPerBlock; ++v) {
+                const unsigned cnt = s_pos[v][k];
+                s_pos[v][k] = sum;
+                sum += cnt;
+            }
+            const unsigned base = sum ? atomicAdd(live + k, sum) : 0u;
+            for (int v = 0; v < kWavesPerBlock; ++v)
+                s_pos[v][k] += base;
+        }
+        __syncthreads();
+        // pass 2: ranks and writes
+#pragma unroll
+        for (int step = 0; step < kSteps; ++step) {
+            const uint64_t any = __ballot(ok[step]);
+            if (any == 0)
+                continue;
+            const unsigned c = cs[step];
+            const LaneRuns r = lane_runs(c, ok[step], any);
+            unsigned start = 0;
+            if ((r.starts >> lane) & 1ull)
+                start = atomicAdd(&s_pos[w][c], r.len);
+            start = __shfl(start, r.first);
+            if (ok[step]) {
+                const unsigned rank = start + (unsigned)(lane - r.first);
+                const unsigned pos = offsets[level * heads + c] + rank;
+                // within the head's stretch whenever the totals are consistent
+                if (rank < totals[level * heads + c] && pos < num_samples)
+                    bucket[pos] = sid[step];
+            }
+        }
+        __syncthreads();  // the counters are cleared by the next stretch
     }
 }
 
@@ -1764,11 +1781,13 @@ hipError_t launch_level_head_order(const RenderGeometry &g, unsigned levels, int
 hipError_t launch_level_compact(const RenderGeometry &g, unsigned level, unsigned levels,
                                 int heads, const unsigned *order,
                                 const unsigned *offsets, const unsigned *totals,
-                                const uint8_t *lvl, const uint8_t *cell, unsigned num_blocks,
+                                const uint8_t *lvl, const uint8_t *cell,
+                                unsigned long long max_entries,
                                 unsigned *live, unsigned *bucket, unsigned *mlp_queue,
                                 hipStream_t s)
 {
-    level_compact_kernel<<<num_blocks, kThreads, 0, s>>>(order, offsets, totals, lvl, cell, level,
+    const unsigned num_blocks = std::min(blocks_for(max_entries, kCompactBlock), 1024u);
+    level_compact_kernel<<<num_blocks, kCompactThreads, 0, s>>>(order, offsets, totals, lvl, cell, level,
                                                          levels, heads, g.num_samples,
                                                          live, bucket, mlp_queue);
     return hipGetLastError();

@@ -300,3 +300,28 @@ def test_culled_argument_errors():
     derf.derf_render_culled(r.handle, o[:0], d[:0], cfg.near, cfg.far, samp, 1e-3, 4, *out)
     torch.cuda.synchronize()
     r.close()
+
+
+@pytest.mark.parametrize("rays", [85, 1365, 1366, 5461])
+def test_compaction_block_edges(rays):
+    """Pieces of 12 in levels whose entries end just short of and just past the
+    compaction's blocks of 16,384 (1,365 rays are 16,380 entries, 1,366 are
+    16,392; 5,461 rays take four blocks), one head, so one counter."""
+    from paper_2011_12490_amd import derf
+    arch, n = scenes.ARCH_TINY, 48
+    w = scenes.make_weights(arch, 1, sigma_bias=6.0)
+    sites = scenes.make_sites("uniform", 1)
+    rng = np.random.Generator(np.random.PCG64(rays))
+    o = rng.uniform(-1.0, 1.0, (rays, 3)).astype(np.float32)
+    d = rng.uniform(-1.0, 1.0, (rays, 3)).astype(np.float32)
+    for levels in (3, 4):  # the last level holds one piece, or none
+        ref = oracle.render_culled(sites, arch, w, o, d, 0.0, 1.0, n, 0.1, levels, seed=2, piece=12)
+        r = derf.Renderer(sites, arch, w, "fp32")
+        got = r.render_culled(torch.from_numpy(o).cuda(), torch.from_numpy(d).cuda(), 0.0, 1.0, n,
+                              0.1, levels, seed=2, piece=12)
+        torch.cuda.synchronize()
+        r.close()
+        same = got[3].cpu().numpy() == ref.evaluated
+        assert same.mean() >= 0.99
+        for x, y in zip(got[:3], (ref.rgb, ref.depth, ref.opacity)):
+            assert np.abs(x.cpu().numpy() - y)[same].max() <= 1e-4
