@@ -1,0 +1,86 @@
+"""The bucketing of small frames (blocks of 1024 samples, counts scanned inside
+the scatter) at its edges, against the same rays in other block sizes."""
+import numpy as np
+import pytest
+
+from paper_2011_12490_amd import scenes
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+
+
+# 2^20 samples are the last small frame: 1,024 blocks, so 8 heads are the last
+# whose 8,192 counts the scatter scans itself; 40 heads walk their rays
+@pytest.mark.parametrize("heads", [1, 8, 9, 40, 256])
+@pytest.mark.parametrize("rays,n", [(1, 1), (1, 1023), (3, 341), (5, 205), (4099, 7),
+                                    (16384, 64), (16385, 64), (33000, 64)])
+def test_blocks_and_scans_agree(heads, rays, n):
+    """A frame equals its halves rendered one by one, bitwise, and every sample
+    is bucketed once (head counts)."""
+    from paper_2011_12490_amd import derf
+    rng = np.random.Generator(np.random.PCG64(heads + rays))
+    sites = rng.uniform(-1.0, 1.0, (heads, 3)).astype(np.float32)
+    r = derf.Renderer(sites, scenes.ARCH_TINY,
+                      scenes.make_weights(scenes.ARCH_TINY, heads, sigma_bias=1.0), "bf16")
+    o = torch.from_numpy(rng.uniform(-1.0, 1.0, (rays, 3)).astype(np.float32)).cuda()
+    d = torch.from_numpy(rng.uniform(-0.5, 0.5, (rays, 3)).astype(np.float32)).cuda()
+    whole = r.render(o, d, 0.0, 1.0, n, seed=5)
+    assert sum(derf.derf_get_stats(r.handle).head_samples[:heads]) == rays * n
+    cut = rays // 2
+    for a, b in ((0, cut), (cut, rays)):
+        if a == b:
+            continue
+        part = r.render(o[a:b].contiguous(), d[a:b].contiguous(), 0.0, 1.0, n, seed=5, ray_offset=a)
+        torch.cuda.synchronize()
+        for x, y in zip(whole, part):
+            assert torch.equal(x[a:b], y)
+    # fine samples: a coarse pass of small blocks beside a fine one of large
+    if n > 1:
+        r.render(o, d, 0.0, 1.0, n, 2 * n if 3 * n <= 1024 else 1, seed=5)
+        got = sum(derf.derf_get_stats(r.handle).head_samples[:heads])
+        assert got == rays * (n + (2 * n if 3 * n <= 1024 else 1))
+    r.close()
+
+
+def test_noalloc_takes_the_same_frames():
+    """256 heads at the largest frame the scratch holds in blocks of 4096: its
+    longer counts would not fit, and it is rendered all the same."""
+    from paper_2011_12490_amd import derf
+    heads, n = 256, 192
+    rng = np.random.Generator(np.random.PCG64(1))
+    sites = rng.uniform(-1.0, 1.0, (heads, 3)).astype(np.float32)
+    r = derf.Renderer(sites, scenes.ARCH_TINY, scenes.make_weights(scenes.ARCH_TINY, heads), "bf16")
+    out = [torch.empty(s, device="cuda") for s in ((8192 * 2, 3), (8192 * 2,), (8192 * 2,))]
+
+    def takes(rays):
+        o = torch.from_numpy(rng.uniform(-1.0, 1.0, (rays, 3)).astype(np.float32)).cuda()
+        try:
+            derf.derf_render_noalloc(r.handle, o, o, 0.0, 1.0, derf.derf_sampling(n, 0, 1, 1, 0), *out)
+        except derf.DerfError as e:
+            assert e.status == derf.DERF_ERR_INVALID_ARG
+            return False
+        torch.cuda.synchronize()
+        return True
+
+    lo, hi = 1, 8192 * 2
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if takes(mid) else (lo, mid)
+
+    # the workspace in blocks of 4096, as the library lays it out
+    def need(rays):
+        s = rays * n
+        nblk = -(-s // 4096)
+        up = lambda b: -(-b // 256) * 256
+        return sum(up(b) for b in (4 * s, s + 16, 16 * s, 0, 0, 0, 4 * s, rays * 64,
+                                   4 * nblk * heads, 4 * heads, 4 * heads, 128, rays * 512, rays))
+
+    assert need(lo) <= derf.DERF_NOALLOC_SCRATCH_BYTES < need(hi)
+    r.close()
