@@ -292,6 +292,15 @@ struct Cfg {
         }
         return cnt;
     }
+    // weight loads of a wave in stages 0 .. LA - 1 (at least: the head block's
+    // share differs by wave)
+    static constexpr int first_loads()
+    {
+        int cnt = 0;
+        for (int x = 0; x < LA; ++x)
+            cnt += st_lpw(x);
+        return cnt < 63 ? cnt : 63;
+    }
     // loads this wave issues after the S_PB prefetch until the next tile
     // starts (it has one: its records were prefetched)
     static constexpr int loads_after_pb()
@@ -961,9 +970,10 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
 
     // Tiles are handed out dynamically.  The tile range is cut into 8
     // contiguous stretches, one per XCD (each XCD has its own L2, and a
-    // stretch covers few heads).  Workgroup b's first tile is fixed: the
-    // (b / 8)-th of stretch b % 8 (workgroups go to the XCDs in turn), so a
-    // launch of at most one tile per workgroup takes none from the queues.
+    // stretch covers few heads).  Workgroup b's first two tiles are fixed: of
+    // stretch b % 8 (workgroups go to the XCDs in turn) the (b / 8)-th and, n
+    // workgroups sharing the stretch, the (n + b / 8)-th, so that no
+    // workgroup's start waits for the others' atomics.
     // queue[x] counts the tiles taken from stretch x after those; a workgroup
     // takes from its own XCD's stretch, then from the others.  The two
     // workgroups sharing a CU do not get equal shares of its matrix pipe, so
@@ -1022,23 +1032,24 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
     auto q_base = [&](unsigned x) { return (unsigned)(((unsigned long long)total_tiles * x) / 8); };
     if (tid < kMlpQueues) {
         const unsigned x = (unsigned)tid, base = q_base(x), len = q_base(x + 1) - base;
-        const unsigned fixed = (gridDim.x + 7u - x) >> 3;  // first tiles that are fixed
-        s_qfirst[x] = base + fixed;
-        s_qcount[x] = len > fixed ? len - fixed : 0u;
-        if (x == (blockIdx.x & 7u))
-            s_q[0] = (blockIdx.x >> 3) < len ? base + (blockIdx.x >> 3) : kNoTile;
+        const unsigned share = (gridDim.x + 7u - x) >> 3, j = blockIdx.x >> 3;
+        s_qfirst[x] = base + 2 * share;
+        s_qcount[x] = len > 2 * share ? len - 2 * share : 0u;
+        if (x == (blockIdx.x & 7u)) {
+            s_q[0] = j < len ? base + j : kNoTile;
+            s_q[1] = share + j < len ? base + share + j : kNoTile;
+        }
     }
     __syncthreads();
     if (tid == 0) {
         own = s_qcount[xcc];
         own_first = s_qfirst[xcc];
-        unsigned first = s_q[0];
-        if (first == kNoTile)
-            s_q[0] = first = steal();
-        unsigned u = 0;
-        if (first != kNoTile && own)
-            u = atomicAdd(queue + xcc, 1u);
-        s_q[1] = first != kNoTile ? take_rest(u) : kNoTile;
+        // stretches differ by a tile, so one may have more than its fixed ones
+        // where another has none for this workgroup
+        if (s_q[0] == kNoTile)
+            s_q[0] = steal();
+        else if (s_q[1] == kNoTile)
+            s_q[1] = steal();
     }
     __syncthreads();
     unsigned tile = __builtin_amdgcn_readfirstlane(s_q[0]);
@@ -1125,16 +1136,23 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
 
     int head = head_of(tile);
     const unsigned char *stream = stream_of(head);
-    // the first tile's records, waited for in full
+    // the first tile's head block and weights go out beside its sample ids, and
+    // its rays' records once the ids are here
+    auto load_block = [&](int h) {
+        const unsigned char *src = reinterpret_cast<const unsigned char *>(blocks + (size_t)h * C::BLOCK_FLOATS);
+        for (int u = wave; u < C::BLOCK_UNITS; u += C::WAVES)
+            load_lds16(src + u * 1024, lane * 16, reinterpret_cast<unsigned char *>(hb) + u * 1024);
+    };
     prefetch_ids(__builtin_amdgcn_readfirstlane(s_off[head] + (tile - s_tile[head]) * C::TILE),
                  __builtin_amdgcn_readfirstlane(min(head_end(head), row_cap)),
                  soft ? s_off[head] : 0u);
-    wait_vmcnt<0>();
-    prefetch_rays();
-    wait_vmcnt<0>();
+    load_block(head);
     unsigned ring = 0;  // ring slot of stage 0 of the current tile (mod NBUF)
     static_for<0, C::LA>([&](auto sc) { issue(sc, stream, ring + decltype(sc)::value); });
-    int loaded_head = -1;
+    wait_vmcnt<C::first_loads()>();  // the ids, issued before the weights
+    prefetch_rays();
+    wait_vmcnt<0>();
+    int loaded_head = head;
 
     while (tile != kNoTile) {
         const bool has_next = next != kNoTile;
@@ -1164,9 +1182,7 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
         if (tid == 0 && has_next && own)
             q_first = atomicAdd(queue + q_own, 1u);
         if (head != loaded_head) {
-            const unsigned char *src = reinterpret_cast<const unsigned char *>(blocks + (size_t)head * C::BLOCK_FLOATS);
-            for (int u = wave; u < C::BLOCK_UNITS; u += C::WAVES)
-                load_lds16(src + u * 1024, lane * 16, reinterpret_cast<unsigned char *>(hb) + u * 1024);
+            load_block(head);
             loaded_head = head;
         }
 
