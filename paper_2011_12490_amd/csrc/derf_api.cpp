@@ -733,13 +733,10 @@ size_t layout_culled(char *base, unsigned S, unsigned R, unsigned nblk, int K, b
 int render_culled_impl(derf_handle *h, const float *rays_o, const float *rays_d,
                        long long num_rays, float near_t, float far_t, const derf_sampling *samp,
                        float eps, int levels, int piece, float *out_rgb, float *out_depth,
-                       float *out_opacity, unsigned *out_evaluated, void *stream,
-                       bool gated = false, int *out_cell = nullptr)
+                       float *out_opacity, unsigned *out_evaluated, void *stream)
 {
     if (!h)
         return fail(DERF_ERR_INVALID_ARG, "null handle");
-    if (gated && !h->gate_w)
-        return fail(DERF_ERR_INVALID_ARG, "no gating network set (derf_set_gate)");
     if (!samp)
         return fail(DERF_ERR_INVALID_ARG, "null sampling descriptor");
     if (num_rays < 0 || num_rays >= (1LL << 30))
@@ -757,7 +754,7 @@ int render_culled_impl(derf_handle *h, const float *rays_o, const float *rays_d,
     if (samp->n_fine != 0)
         return fail(DERF_ERR_UNSUPPORTED, "the culled render has no hierarchical sampling");
     if (h->gx_bytes)
-        return fail(DERF_ERR_UNSUPPORTED, "the culled and gated renders have no stored encoding");
+        return fail(DERF_ERR_UNSUPPORTED, "the culled render has no stored encoding");
     if (num_rays == 0)
         return DERF_OK;
     if (!rays_o || !rays_d || !out_rgb || !out_depth || !out_opacity)
@@ -769,8 +766,7 @@ int render_culled_impl(derf_handle *h, const float *rays_o, const float *rays_d,
     HIP_TRY(hipSetDevice(h->device), "hipSetDevice");
     const unsigned R = (unsigned)num_rays, N = (unsigned)samp->n_coarse, S = R * N;
     const unsigned L = (unsigned)levels, nblk = blocks_of(S);
-    if (!gated && (L == 1 || eps == 0.0f ||
-                   (h->num_sites == 1 && (piece == 0 || (unsigned)piece >= N)))) {
+    if (L == 1 || eps == 0.0f || (h->num_sites == 1 && (piece == 0 || (unsigned)piece >= N))) {
         // Nothing can stop a ray (one level; eps = 0, which every
         // transmittance passes; or one head in whole segments, where level 0
         // is the whole ray): the single pass, derf_render's outputs bitwise,
@@ -821,29 +817,21 @@ int render_culled_impl(derf_handle *h, const float *rays_o, const float *rays_d,
         return hipEventRecord(h->ev[ev_index(0, stage, end)], s);
     };
     HIP_TRY(mark(DERF_STAGE_SAMPLE, 0), "hipEventRecord");
-    if (gated)
-        HIP_TRY(launch_ray_encode(g, b.dirbuf, h->bf16, s), "ray_encode launch");
-    // the gated assignment draws the depths itself and needs no nearest site
-    const WalkTable walk{gated ? nullptr : b.walk_seg, gated ? nullptr : b.walk_nseg};
-    if (gated) {
-        HIP_TRY(launch_gate(g, h->gate_w, h->gate_freqs, h->gate_hidden, K, b.t, b.cell, out_cell,
-                            h->mlp_grid, s),
-                "gate launch");
-    } else {
-        if (walk.seg)
-            HIP_TRY(launch_ray_walk(g, h->sites, K, b.walk_seg, b.walk_nseg, s),
-                    "ray_walk launch");
-        HIP_TRY(launch_sample_assign(g, h->sites, K, walk, b.t, b.cell, b.counts, nblk,
-                                     kBucketBlock, DirOut{b.dirbuf, h->bf16}, s),
-                "sample_assign launch");
-    }
-    HIP_TRY(launch_level_bounds(b.cell, N, R, L, P, c.lb, c.lvl, s),
+    const WalkTable walk{b.walk_seg, b.walk_nseg};
+    if (walk.seg)
+        HIP_TRY(launch_ray_walk(g, h->sites, K, b.walk_seg, b.walk_nseg, s), "ray_walk launch");
+    HIP_TRY(launch_sample_assign(g, h->sites, K, walk, b.t, b.cell, b.counts, nblk, kBucketBlock,
+                                 DirOut{b.dirbuf, h->bf16}, s),
+            "sample_assign launch");
+    // levels below the last count their rays' runs into zeroed counts
+    const bool one_pass = one_pass_levels(L, K, P);
+    const unsigned clear_count = one_pass ? 0u : nblk * (unsigned)K;
+    HIP_TRY(launch_level_bounds(b.cell, N, R, L, P, c.lb, c.lvl, b.counts, clear_count, s),
             "level_bounds launch");
     // Levels cut into pieces: bucket every sample by (level, head) once; each
     // level after the first then compacts only its own samples, dropping
     // those of closed rays.  Otherwise each level counts and scatters its
     // live samples.
-    const bool one_pass = one_pass_levels(L, K, P);
     if (one_pass) {
         HIP_TRY(launch_level_head_order(g, L, K, c.lvl, b.cell, h->empty, c.key_counts,
                                         nblk, c.key_totals, c.order, c.key_offsets,
@@ -874,7 +862,7 @@ int render_culled_impl(derf_handle *h, const float *rays_o, const float *rays_d,
         } else if (l + 1 < L) {
             // one run of one cell per open ray: bucketed ray by ray
             HIP_TRY(launch_level_ray_bucket(g, b.cell, K, h->empty, lv, b.counts, nblk, tot,
-                                            b.totals, b.bucket, b.sr, b.mlp_queue, s),
+                                            b.bucket, b.sr, b.mlp_queue, s),
                     "level_ray_bucket launch");
             HIP_TRY(launch_groups(h, b.bucket, tot, g, b.t, b.dirbuf, b.sr, b.mlp_queue, false, s),
                     "mlp launch");
@@ -891,7 +879,8 @@ int render_culled_impl(derf_handle *h, const float *rays_o, const float *rays_d,
         }
         // every level but the last is one piece of at most P samples
         HIP_TRY(launch_level_composite(g, b.t, b.cell, b.sr, lv, l + 1 < L ? P : 0u, out_rgb,
-                                       out_depth, out_opacity, s),
+                                       out_depth, out_opacity, b.counts,
+                                       l + 2 < L ? clear_count : 0u, s),
                 "level_composite launch");
     }
     HIP_TRY(mark(DERF_STAGE_MLP, 1), "hipEventRecord");
@@ -902,6 +891,110 @@ int render_culled_impl(derf_handle *h, const float *rays_o, const float *rays_d,
     h->totals_sets = levels;
     h->walk_nseg = walk.nseg;
     h->walk_rays = walk.nseg ? R : 0;
+    h->stats.renders += 1;
+    h->stats.samples += (long long)S;
+    return DERF_OK;
+}
+
+// MLP gating (Sec. 4): depths and heads from the gating network, then the
+// single pass's bucketing, MLP and composite, none of which assume convex cells
+// (a ray may come back to a head: another run of it).
+int render_gated_impl(derf_handle *h, const float *rays_o, const float *rays_d,
+                      long long num_rays, float near_t, float far_t, const derf_sampling *samp,
+                      float *out_rgb, float *out_depth, float *out_opacity, int *out_cell,
+                      void *stream)
+{
+    if (!h)
+        return fail(DERF_ERR_INVALID_ARG, "null handle");
+    if (!h->gate_w)
+        return fail(DERF_ERR_INVALID_ARG, "no gating network set (derf_set_gate)");
+    if (!samp)
+        return fail(DERF_ERR_INVALID_ARG, "null sampling descriptor");
+    if (num_rays < 0 || num_rays >= (1LL << 30))
+        return fail(DERF_ERR_INVALID_ARG, "need 0 <= num_rays < 2^30");
+    if (!(near_t < far_t) || !isfinite(near_t) || !isfinite(far_t))
+        return fail(DERF_ERR_INVALID_ARG, "need finite near < far");
+    if (samp->n_coarse < 1 || samp->n_coarse > 1024 || samp->n_fine < 0)
+        return fail(DERF_ERR_INVALID_ARG, "need 1 <= n_coarse <= 1024, n_fine >= 0");
+    if (samp->n_fine != 0)
+        return fail(DERF_ERR_UNSUPPORTED, "the gated render has no hierarchical sampling");
+    if (h->gx_bytes)
+        return fail(DERF_ERR_UNSUPPORTED, "the gated render has no stored encoding");
+    if (num_rays == 0)
+        return DERF_OK;
+    if (!rays_o || !rays_d || !out_rgb || !out_depth || !out_opacity)
+        return fail(DERF_ERR_INVALID_ARG, "null ray or output pointer");
+    if ((unsigned long long)num_rays * (unsigned)samp->n_coarse >= (1ull << 32))
+        return fail(DERF_ERR_INVALID_ARG, "num_rays * n_coarse must be < 2^32 per call");
+
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    HIP_TRY(hipSetDevice(h->device), "hipSetDevice");
+    const unsigned R = (unsigned)num_rays, N = (unsigned)samp->n_coarse, S = R * N;
+    const unsigned block = bucket_block(S), nblk = blocks_of(S, block);
+    const int K = h->num_sites;
+    int rc = ensure_workspace(h, layout(nullptr, S, 0, R, nblk, K, h->bf16, 0, nullptr));
+    if (rc != DERF_OK)
+        return rc;
+    if (h->timing && h->ev_pending) {
+        HIP_TRY(hipEventSynchronize(last_event(h)), "hipEventSynchronize");
+        accumulate_timing(h);
+    }
+    Buffers b;
+    layout(reinterpret_cast<char *>(h->ws.mem), S, 0, R, nblk, K, h->bf16, 0, &b);
+
+    RenderGeometry g;
+    g.rays_o = rays_o;
+    g.rays_d = rays_d;
+    g.num_rays = R;
+    g.n = N;
+    g.num_samples = S;
+    g.inv_n = 1.0 / (double)N;
+    g.near_t = near_t;
+    g.far_t = far_t;
+    g.step = (far_t - near_t) / (float)N;
+    g.seed = samp->seed;
+    g.ray_offset = samp->ray_offset;
+    g.perturb = samp->perturb ? 1 : 0;
+
+    h->ev_mask = 0;
+    auto mark = [&](int stage, int end) -> hipError_t {
+        if (!h->timing)
+            return hipSuccess;
+        h->ev_mask |= 1u << stage;
+        return hipEventRecord(h->ev[ev_index(0, stage, end)], s);
+    };
+    HIP_TRY(mark(DERF_STAGE_SAMPLE, 0), "hipEventRecord");
+    HIP_TRY(launch_ray_encode(g, b.dirbuf, h->bf16, s), "ray_encode launch");
+    HIP_TRY(launch_gate(g, h->gate_w, h->gate_freqs, h->gate_hidden, K, b.t, b.cell, out_cell,
+                        h->mlp_grid, s),
+            "gate launch");
+    HIP_TRY(mark(DERF_STAGE_SAMPLE, 1), "hipEventRecord");
+    // (one stage for all that follows, as the culled render's level loop)
+    HIP_TRY(mark(DERF_STAGE_MLP, 0), "hipEventRecord");
+    HIP_TRY(launch_cell_count(g, b.cell, K, b.counts, nblk, block, s), "cell_count launch");
+    if ((unsigned long long)nblk * K <= kScanInScatter) {
+        HIP_TRY(launch_bucket_scan_scatter(b.cell, b.counts, b.totals, b.mlp_queue, S, nblk, block,
+                                           K, h->empty, b.bucket, b.sr, s),
+                "bucket_scan_scatter launch");
+    } else {
+        HIP_TRY(launch_bucket_scan(b.counts, nblk, K, b.totals, b.mlp_queue, s),
+                "bucket_scan launch");
+        HIP_TRY(launch_bucket_scatter(b.cell, b.counts, b.totals, S, nblk, block, K, h->empty,
+                                      b.bucket, b.sr, s),
+                "bucket_scatter launch");
+    }
+    HIP_TRY(launch_groups(h, b.bucket, b.totals, g, b.t, b.dirbuf, b.sr, b.mlp_queue, false, s),
+            "mlp launch");
+    HIP_TRY(launch_composite(g, b.t, b.cell, b.sr, out_rgb, out_depth, out_opacity, s),
+            "composite launch");
+    HIP_TRY(mark(DERF_STAGE_MLP, 1), "hipEventRecord");
+    h->ev_pending = h->timing;
+    h->last_stream = s;
+    h->totals = b.totals;
+    h->totals_fine = nullptr;
+    h->totals_sets = 1;
+    h->walk_nseg = nullptr;
+    h->walk_rays = 0;
     h->stats.renders += 1;
     h->stats.samples += (long long)S;
     return DERF_OK;
@@ -1200,9 +1293,8 @@ int derf_render_gated(derf_handle *h, const float *rays_o, const float *rays_d,
                       float *out_rgb, float *out_depth, float *out_opacity, int *out_cell,
                       void *hip_stream)
 {
-    return render_culled_impl(h, rays_o, rays_d, num_rays, near_t, far_t, samp, 0.0f, 1, 0,
-                              out_rgb, out_depth, out_opacity, nullptr, hip_stream, true,
-                              out_cell);
+    return render_gated_impl(h, rays_o, rays_d, num_rays, near_t, far_t, samp, out_rgb, out_depth,
+                             out_opacity, out_cell, hip_stream);
 }
 
 int derf_set_empty_heads(derf_handle *h, const int *flags)

@@ -24,9 +24,11 @@ struct CullLevel {
     float eps;
 };
 constexpr int kMaxLevels = 32;
+// clear, clear_count (here and at launch_level_composite): words to set to
+// zero for a later kernel, or null, 0
 hipError_t launch_level_bounds(const uint8_t *cell, unsigned n, unsigned num_rays,
                                unsigned levels, unsigned piece, unsigned *lb, uint8_t *lvl,
-                               hipStream_t s);
+                               unsigned *clear, unsigned clear_count, hipStream_t s);
 // per-block head counts of the samples live at the level (the layout of the
 // assignment's counts)
 hipError_t launch_level_count(const RenderGeometry &g, const uint8_t *cell, int num_sites,
@@ -58,15 +60,15 @@ hipError_t launch_level_compact(const RenderGeometry &g, unsigned level, unsigne
 // such a level are one run of one cell, touching at most two blocks): the
 // runs are counted into counts [K][num_blocks] (the per-sample counts'
 // layout), scanned by bucket_scan into per-block prefixes and totals [K],
-// and written to bucket at head_off [K] (K words of scratch: the exclusive
-// scan of the totals) plus a position reserved from the prefix of their
-// block (runs of one block in no fixed order).  sr gets zeros for
-// 0-capacity heads.  Clears the MLP's tile counters.
+// and written to bucket at their head's offset plus a position reserved from
+// the prefix of their block (runs of one block in no fixed order).  counts
+// must be zero on entry (cleared by launch_level_bounds, or by the previous
+// level's launch_level_composite).  sr gets zeros for 0-capacity heads.
+// Clears the MLP's tile counters.
 hipError_t launch_level_ray_bucket(const RenderGeometry &g, const uint8_t *cell, int num_sites,
                                    const HeadMask &empty, const CullLevel &lv, unsigned *counts,
-                                   unsigned num_blocks, unsigned *totals, unsigned *head_off,
-                                   unsigned *bucket, float4 *sr, unsigned *mlp_queue,
-                                   hipStream_t s);
+                                   unsigned num_blocks, unsigned *totals, unsigned *bucket,
+                                   float4 *sr, unsigned *mlp_queue, hipStream_t s);
 // bucket_scatter over the samples live at the level
 hipError_t launch_level_scatter(const RenderGeometry &g, const uint8_t *cell,
                                 const unsigned *counts, const unsigned *totals,
@@ -80,6 +82,7 @@ hipError_t launch_level_scatter(const RenderGeometry &g, const uint8_t *cell,
 // the others 16.
 hipError_t launch_level_composite(const RenderGeometry &g, const float *t, const uint8_t *cell,
                                   const float4 *sr, const CullLevel &lv, unsigned max_len,
-                                  float *rgb, float *depth, float *opacity, hipStream_t s);
+                                  float *rgb, float *depth, float *opacity, unsigned *clear,
+                                  unsigned clear_count, hipStream_t s);
 
 }  // namespace derf

@@ -111,6 +111,9 @@ hipError_t launch_assign_given(const RenderGeometry &g, const float4 *sites, int
                                const WalkTable &walk, const float *t,
                                uint8_t *cell, unsigned *counts, unsigned num_blocks,
                                unsigned block, hipStream_t s);
+// The counts of given cells (the layout of the assignment's).
+hipError_t launch_cell_count(const RenderGeometry &g, const uint8_t *cell, int num_sites,
+                             unsigned *counts, unsigned num_blocks, unsigned block, hipStream_t s);
 // also clears the kMlpQueues tile counters of the MLP launch that follows
 hipError_t launch_bucket_scan(unsigned *counts, unsigned num_blocks, int num_sites,
                               unsigned *totals, unsigned *mlp_queue, hipStream_t s);

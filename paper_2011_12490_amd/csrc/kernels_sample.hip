@@ -738,6 +738,37 @@ __global__ __launch_bounds__(1024) void bucket_scan_kernel(unsigned *__restrict_
         totals[blockIdx.x] = s_carry;
 }
 
+// off[k] = the sum of the totals below k, by wave 0, 4 heads per lane (K <=
+// 256), the loads in flight together.
+__device__ __forceinline__ void head_offsets(const unsigned *totals, int num_sites, unsigned *off)
+{
+    if (threadIdx.x >= 64)
+        return;
+    const int lane = threadIdx.x;
+    unsigned t[4], sum = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int k = 4 * lane + j;
+        t[j] = k < num_sites ? totals[k] : 0u;
+        sum += t[j];
+    }
+    unsigned incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned y = __shfl_up(incl, o);
+        if (lane >= o)
+            incl += y;
+    }
+    unsigned acc = incl - sum;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int k = 4 * lane + j;
+        if (k < num_sites)
+            off[k] = acc;
+        acc += t[j];
+    }
+}
+
 // First bucket position of each head's part in block b: the heads below k
 // take sum_{j<k} totals_j entries, and within head k the blocks before b
 // take prefix[k][b] (exclusive scan over blocks).  Computed by wave 0, 4
@@ -870,6 +901,18 @@ struct LevelLive {
 // all levels at once.
 constexpr int kCellKey = 0, kCellAtLevel = 1, kLevelCell = 2;
 
+// Words that a kernel with threads to spare clears for a later one on the
+// stream (a launch of its own took 5 us).
+struct ClearWords {
+    unsigned *p;
+    unsigned count;
+    __device__ __forceinline__ void run() const
+    {
+        for (unsigned i = blockIdx.x * kThreads + threadIdx.x; i < count; i += gridDim.x * kThreads)
+            p[i] = 0;
+    }
+};
+
 // Level bounds, one wave per ray, 64 samples per step.  A sample opens a
 // segment when its cell differs from the previous sample's.  With piece > 0 a
 // sample also opens a piece when it lies a multiple of piece samples past the
@@ -889,8 +932,10 @@ __global__ __launch_bounds__(kThreads) void level_bounds_kernel(const uint8_t *_
                                                                unsigned n, unsigned num_rays,
                                                                unsigned levels, unsigned piece,
                                                                unsigned *__restrict__ lb,
-                                                               uint8_t *__restrict__ lvl)
+                                                               uint8_t *__restrict__ lvl,
+                                                               ClearWords clear)
 {
+    clear.run();
     __shared__ uint32_t s_in[WORDS ? kThreads : 1], s_out[WORDS ? kThreads : 1];
     const unsigned lane = threadIdx.x & 63;
     const unsigned ray = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
@@ -972,35 +1017,34 @@ __global__ __launch_bounds__(kThreads) void level_bounds_kernel(const uint8_t *_
 }
 
 // Per-block key histograms (the layout of the assignment's counts:
-// counts[key * num_blocks + b]; num_keys keys), MODE
-// kCellAtLevel or kLevelCell.  Thread t takes samples t + 256 q of the block
-// (q < 16); all 16 level bytes and cells are loaded up front, so the loads
-// are in flight together.
-template <int MODE>
+// counts[key * num_blocks + b]; num_keys keys).  Thread t takes samples
+// t + 256 q of the block (q < BLOCK / 256); all its level bytes and cells are
+// loaded up front, so the loads are in flight together.
+template <int MODE, int BLOCK = kBucketBlock>
 __global__ __launch_bounds__(kThreads) void level_count_kernel(const uint8_t *__restrict__ cell,
                                                               unsigned num_samples, int num_keys,
                                                               LevelLive live,
                                                               unsigned *__restrict__ counts,
                                                               unsigned num_blocks)
 {
-    constexpr int kSteps = kBucketBlock / kThreads;
+    constexpr int kSteps = BLOCK / kThreads;
     __shared__ unsigned s_hist[kMaxSites];
     for (int k = threadIdx.x; k < num_keys; k += kThreads)
         s_hist[k] = 0;
-    const unsigned long long base = (unsigned long long)blockIdx.x * kBucketBlock + threadIdx.x;
+    const unsigned long long base = (unsigned long long)blockIdx.x * BLOCK + threadIdx.x;
     uint8_t lv[kSteps], cs[kSteps];
 #pragma unroll
     for (int q = 0; q < kSteps; ++q) {
         const unsigned long long s64 = base + (unsigned)q * kThreads;
         const bool in = s64 < num_samples;
-        lv[q] = in ? live.lvl[s64] : kDeadLevel;
+        lv[q] = !in ? kDeadLevel : MODE == kCellKey ? (uint8_t)0 : live.lvl[s64];
         cs[q] = in ? cell[s64] : (uint8_t)0;
     }
     __syncthreads();
     const uint64_t lane_bit = 1ull << (threadIdx.x & 63);
 #pragma unroll
     for (int q = 0; q < kSteps; ++q) {
-        const bool ok = MODE == kLevelCell ? lv[q] != kDeadLevel : lv[q] == live.level;
+        const bool ok = MODE == kCellAtLevel ? lv[q] == live.level : lv[q] != kDeadLevel;
         const unsigned key = MODE == kLevelCell ? lv[q] * live.heads + cs[q] : cs[q];
         const uint64_t any = __ballot(ok);
         if (any == 0)
@@ -1068,29 +1112,10 @@ __global__ __launch_bounds__(kThreads) void level_ray_count_kernel(
         atomicAdd(row + b0 + 1, (unsigned)(s1 - split));
 }
 
-// head_off[k] = sum of totals below k (where head k's stretch starts).  One
-// block, K <= 256.
-__global__ __launch_bounds__(kThreads) void head_offsets_kernel(const unsigned *__restrict__ totals,
-                                                                int num_sites,
-                                                                unsigned *__restrict__ head_off)
-{
-    __shared__ unsigned s_v[kThreads];
-    const int t = threadIdx.x;
-    const unsigned v = t < num_sites ? totals[t] : 0u;
-    s_v[t] = v;
-    __syncthreads();
-    for (int o = 1; o < kThreads; o <<= 1) {
-        const unsigned y = t >= o ? s_v[t - o] : 0u;
-        __syncthreads();
-        s_v[t] += y;
-        __syncthreads();
-    }
-    if (t < num_sites)
-        head_off[t] = s_v[t] - v;
-}
-
 // Each open ray's run (in at most two block pieces) goes to head k's
-// stretch at head_off[k] plus a position reserved from the block's prefix
+// stretch, which starts at the sum of the totals below k (scanned here by
+// wave 0 of every block: a launch of its own took 4.6 us a level), plus a
+// position reserved from the block's prefix
 // prefix[k * num_blocks + b] (the scanned counts: rays of one block and
 // head share a counter, so reservations rarely contend).  The wave then
 // writes its pieces one after another with all its lanes (coalesced).
@@ -1100,11 +1125,14 @@ __global__ __launch_bounds__(kThreads) void level_ray_scatter_kernel(
     const uint8_t *__restrict__ cell, const unsigned *__restrict__ lb,
     const float *__restrict__ trans, unsigned n, unsigned num_rays, unsigned num_samples,
     unsigned level, unsigned levels, float eps, HeadMask empty,
-    const unsigned *__restrict__ head_off, unsigned *__restrict__ prefix, unsigned num_blocks,
-    unsigned *__restrict__ bucket, float4 *__restrict__ sr)
+    const unsigned *__restrict__ totals, int num_sites, unsigned *__restrict__ prefix,
+    unsigned num_blocks, unsigned *__restrict__ bucket, float4 *__restrict__ sr)
 {
+    __shared__ unsigned head_off[kMaxSites];
     const RayRun r = level_ray_run(cell, lb, trans, n, num_rays, level, levels, eps);
     const int lane = (int)(threadIdx.x & 63);
+    head_offsets(totals, num_sites, head_off);
+    __syncthreads();
     unsigned pos[2] = {0u, 0u}, len[2] = {0u, 0u};
     if (r.on) {
         const unsigned long long s1 = r.s0 + r.len;
@@ -1463,8 +1491,10 @@ template <int G>
 __global__ __launch_bounds__(kThreads) void level_composite_kernel(
     const float *__restrict__ t, const uint8_t *__restrict__ cell, const float4 *__restrict__ sr,
     unsigned n, unsigned num_rays, float near_t, float far_t, LevelState lv,
-    float *__restrict__ out_rgb, float *__restrict__ out_depth, float *__restrict__ out_opacity)
+    float *__restrict__ out_rgb, float *__restrict__ out_depth, float *__restrict__ out_opacity,
+    ClearWords clear)
 {
+    clear.run();
     constexpr int CH = 4 * G, RPW = 64 / G;  // samples per chunk, rays per wave
     __shared__ float4 s_sr[kThreads / 64][RPW][CH];
     __shared__ float s_t[kThreads / 64][RPW][CH + 2];  // [0]: before the chunk, [len + 1]: after
@@ -1698,15 +1728,16 @@ hipError_t launch_composite(const RenderGeometry &g, const float *t, const uint8
 
 hipError_t launch_level_bounds(const uint8_t *cell, unsigned n, unsigned num_rays,
                                unsigned levels, unsigned piece, unsigned *lb, uint8_t *lvl,
-                               hipStream_t s)
+                               unsigned *clear, unsigned clear_count, hipStream_t s)
 {
     const unsigned grid = blocks_for(num_rays, kThreads / 64);
+    const ClearWords cw{clear, clear_count};
     if (n % 4 == 0 && ((uintptr_t)cell | (uintptr_t)lvl) % 4 == 0)
         level_bounds_kernel<true><<<grid, kThreads, 0, s>>>(cell, n, num_rays, levels, piece, lb,
-                                                            lvl);
+                                                            lvl, cw);
     else
         level_bounds_kernel<false><<<grid, kThreads, 0, s>>>(cell, n, num_rays, levels, piece, lb,
-                                                             lvl);
+                                                             lvl, cw);
     return hipGetLastError();
 }
 
@@ -1714,15 +1745,12 @@ static LevelLive level_live(const CullLevel &lv) { return LevelLive{lv.lvl, lv.l
 
 hipError_t launch_level_ray_bucket(const RenderGeometry &g, const uint8_t *cell, int num_sites,
                                    const HeadMask &empty, const CullLevel &lv, unsigned *counts,
-                                   unsigned num_blocks, unsigned *totals, unsigned *head_off,
-                                   unsigned *bucket, float4 *sr, unsigned *mlp_queue,
-                                   hipStream_t s)
+                                   unsigned num_blocks, unsigned *totals, unsigned *bucket,
+                                   float4 *sr, unsigned *mlp_queue, hipStream_t s)
 {
     if (lv.level + 1 >= lv.levels || num_sites < 1 || num_sites > kMaxSites)
         return hipErrorInvalidValue;
-    hipError_t e = launch_fill_u32(counts, (unsigned)num_sites * num_blocks, 0u, s);
-    if (e != hipSuccess)
-        return e;
+    hipError_t e = hipSuccess;
     const unsigned grid = blocks_for(g.num_rays, kThreads);
     if (grid > 0) {
         level_ray_count_kernel<<<grid, kThreads, 0, s>>>(cell, lv.lb, lv.trans, g.n, g.num_rays,
@@ -1734,14 +1762,23 @@ hipError_t launch_level_ray_bucket(const RenderGeometry &g, const uint8_t *cell,
     if ((e = launch_bucket_scan(counts, num_blocks, num_sites, totals, mlp_queue, s)) !=
         hipSuccess)
         return e;
-    head_offsets_kernel<<<1, kThreads, 0, s>>>(totals, num_sites, head_off);
-    if ((e = hipGetLastError()) != hipSuccess)
-        return e;
     if (grid > 0)
         level_ray_scatter_kernel<<<grid, kThreads, 0, s>>>(
             cell, lv.lb, lv.trans, g.n, g.num_rays, g.num_samples, lv.level, lv.levels, lv.eps,
-            empty, head_off, counts, num_blocks, bucket, sr);
+            empty, totals, num_sites, counts, num_blocks, bucket, sr);
     return hipGetLastError();
+}
+
+hipError_t launch_cell_count(const RenderGeometry &g, const uint8_t *cell, int num_sites,
+                             unsigned *counts, unsigned num_blocks, unsigned block, hipStream_t s)
+{
+    auto go = [&](auto kernel) {
+        kernel<<<num_blocks, kThreads, 0, s>>>(cell, g.num_samples, num_sites, LevelLive{}, counts,
+                                               num_blocks);
+        return hipGetLastError();
+    };
+    return block == (unsigned)kSmallBlock ? go(level_count_kernel<kCellKey, kSmallBlock>)
+                                          : go(level_count_kernel<kCellKey>);
 }
 
 hipError_t launch_level_count(const RenderGeometry &g, const uint8_t *cell, int num_sites,
@@ -1807,18 +1844,20 @@ hipError_t launch_level_scatter(const RenderGeometry &g, const uint8_t *cell,
 
 hipError_t launch_level_composite(const RenderGeometry &g, const float *t, const uint8_t *cell,
                                   const float4 *sr, const CullLevel &lv, unsigned max_len,
-                                  float *rgb, float *depth, float *opacity, hipStream_t s)
+                                  float *rgb, float *depth, float *opacity, unsigned *clear,
+                                  unsigned clear_count, hipStream_t s)
 {
+    const ClearWords cw{clear, clear_count};
     const LevelState st{lv.lb, lv.lvl, lv.trans, lv.evaluated, lv.levels, lv.level, lv.eps};
     // pieces of at most 32 samples: one chunk of 8 lanes per ray; otherwise
     // 16 lanes, in as many chunks of 64 as the range needs
     if (max_len > 0 && max_len <= 32)
         level_composite_kernel<8><<<blocks_for((size_t)g.num_rays * 8, kThreads), kThreads, 0, s>>>(
-            t, cell, sr, g.n, g.num_rays, g.near_t, g.far_t, st, rgb, depth, opacity);
+            t, cell, sr, g.n, g.num_rays, g.near_t, g.far_t, st, rgb, depth, opacity, cw);
     else
         level_composite_kernel<16><<<blocks_for((size_t)g.num_rays * 16, kThreads), kThreads, 0,
                                      s>>>(t, cell, sr, g.n, g.num_rays, g.near_t, g.far_t, st, rgb,
-                                          depth, opacity);
+                                          depth, opacity, cw);
     return hipGetLastError();
 }
 
