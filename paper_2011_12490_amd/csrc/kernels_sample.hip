@@ -126,13 +126,28 @@ __device__ __forceinline__ LaneRuns lane_runs(unsigned key, bool ok, uint64_t va
     return r;
 }
 
+// The same where every lane is valid (a block that the frame fills): about
+// half the instructions.
+__device__ __forceinline__ LaneRuns lane_runs_full(unsigned key)
+{
+    const int lane = (int)(threadIdx.x & 63);
+    const unsigned prev = (unsigned)__builtin_amdgcn_update_dpp(0, (int)key, 0x138, 0xF, 0xF, false);
+    LaneRuns r;
+    r.starts = __ballot(prev != key) | 1ull;
+    const uint64_t brk = r.starts & ~((2ull << lane) - 1ull);
+    r.len = (unsigned)((brk ? __builtin_ctzll(brk) : 64) - lane);
+    r.first = 63 - __builtin_clzll(r.starts & (~0ull >> (63 - lane)));  // (lane 0 starts one)
+    return r;
+}
+
 // out[step] = p[wbase + 64 step + lane], or 0 from index n on: a wave's
 // 64 STEPS consecutive bytes, read as dwords four to a lane (a quarter of
 // the load instructions of one byte per lane, which kept the texture-data
 // path busy) and handed to their lanes by lane permutes.  p + wbase must be
 // 4-byte aligned, and a dword that starts below n must lie in p's
 // allocation (byte buffers are allocated in whole 256-byte units).
-template <int STEPS>
+// FULL: n is known to lie past the wave's last byte.
+template <bool FULL = false, int STEPS>
 __device__ __forceinline__ void wave_bytes(const uint8_t *__restrict__ p, unsigned wbase,
                                            unsigned n, unsigned (&out)[STEPS])
 {
@@ -142,7 +157,7 @@ __device__ __forceinline__ void wave_bytes(const uint8_t *__restrict__ p, unsign
 #pragma unroll
     for (int q = 0; q < STEPS / 4; ++q) {
         const unsigned first = wbase + 256 * q + 4 * lane;
-        word[q] = first < n ? *reinterpret_cast<const unsigned *>(p + first) : 0u;
+        word[q] = FULL || first < n ? *reinterpret_cast<const unsigned *>(p + first) : 0u;
     }
 #pragma unroll
     for (int q = 0; q < STEPS / 4; ++q)
@@ -151,7 +166,7 @@ __device__ __forceinline__ void wave_bytes(const uint8_t *__restrict__ p, unsign
             // byte 256 q + 64 j + lane lies in the dword of lane 16 j + lane / 4
             const unsigned v = (unsigned)__shfl((int)word[q], 16 * j + (lane >> 2));
             const unsigned idx = wbase + 256 * q + 64 * j + lane;
-            out[4 * q + j] = idx < n ? (v >> (8 * (lane & 3))) & 0xFFu : 0u;
+            out[4 * q + j] = FULL || idx < n ? (v >> (8 * (lane & 3))) & 0xFFu : 0u;
         }
 }
 
@@ -558,6 +573,7 @@ void sample_assign_kernel(
 
     const uint2 key = make_uint2((unsigned)g.seed, (unsigned)(g.seed >> 32));
     const uint64_t lane_bit = 1ull << (threadIdx.x & 63);
+    const bool full = (unsigned long long)block_base + BLOCK <= g.num_samples;
     for (int round = 0; round < BLOCK / (4 * kThreads); ++round) {
         const unsigned s0 = block_base + round * (4 * kThreads) + 4 * threadIdx.x;
         unsigned r, i;
@@ -632,7 +648,7 @@ void sample_assign_kernel(
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const bool ok = s0 + v < g.num_samples;
-            const LaneRuns r = lane_runs(cv[v], ok, __ballot(ok));
+            const LaneRuns r = full ? lane_runs_full(cv[v]) : lane_runs(cv[v], ok, __ballot(ok));
             if ((r.starts & lane_bit) != 0)
                 atomicAdd(&s_hist[cv[v]], r.len);
         }
@@ -1189,7 +1205,7 @@ __global__ __launch_bounds__(kThreads) void level_ray_scatter_kernel(
 // holds the counts themselves, and the kernel scans them (totals and mlp_queue
 // are outputs then).
 template <int MODE, int BLOCK = kBucketBlock, bool SCAN = false>
-__global__ __launch_bounds__(kThreads) void bucket_scatter_kernel(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void bucket_scatter_kernel(
     const uint8_t *__restrict__ cell, const unsigned *__restrict__ prefix,
     unsigned *__restrict__ totals, unsigned num_samples, unsigned num_blocks,
     int num_sites, HeadMask empty, LevelLive live, unsigned *__restrict__ bucket,
@@ -1210,67 +1226,83 @@ __global__ __launch_bounds__(kThreads) void bucket_scatter_kernel(
     for (int k = threadIdx.x; k < num_sites; k += kThreads)
         for (int v = 0; v < kWavesPerBlock; ++v)
             s_pos[v][k] = 0;
-    const unsigned wbase = blockIdx.x * (unsigned)BLOCK + w * (kSteps * 64);
-    unsigned cs[kSteps];
-    bool in[kSteps];  // the sample exists (LEVEL: and is live at this level)
-    wave_bytes(cell, wbase, num_samples, cs);
-    unsigned lv[MODE == kCellKey ? 1 : kSteps];
-    if constexpr (MODE != kCellKey)
-        wave_bytes(live.lvl, wbase, num_samples, lv);
+    unsigned any_empty = 0;
+    for (unsigned word : empty.w)
+        any_empty |= word;
+    // FULL: the block's samples all exist (and take part: kCellKey), so that
+    // no step looks for those that do not.  The kernel is bound by its VALU
+    // instructions (1,252 a wave of 1024 samples without this), not by the
+    // bytes it moves: 2^28 samples of 64 heads 594 -> 446 us, 413 us at 7
+    // waves per SIMD (13 registers spilled, against 86 and 5 waves); 36.6 M
+    // samples of 16 heads 67 -> 50 us.
+    auto scatter = [&](auto full) {
+        constexpr bool FULL = decltype(full)::value;
+        const unsigned wbase = blockIdx.x * (unsigned)BLOCK + w * (kSteps * 64);
+        unsigned cs[kSteps];
+        bool in[kSteps];  // the sample exists (LEVEL: and is live at this level)
+        wave_bytes<FULL>(cell, wbase, num_samples, cs);
+        unsigned lv[MODE == kCellKey ? 1 : kSteps];
+        if constexpr (MODE != kCellKey)
+            wave_bytes(live.lvl, wbase, num_samples, lv);
 #pragma unroll
-    for (int step = 0; step < kSteps; ++step) {
-        in[step] = wbase + step * 64 + lane < num_samples;
-        if constexpr (LEVEL)
-            in[step] = in[step] && lv[step] == live.level;
-        if constexpr (MODE == kLevelCell)
-            cs[step] += in[step] ? lv[step] * live.heads : 0u;
-    }
-    __syncthreads();
-    // pass 1: this wave's count per head (run leaders)
-#pragma unroll
-    for (int step = 0; step < kSteps; ++step) {
-        const bool ok = in[step];
-        const uint64_t any = __ballot(ok);
-        if (LEVEL && any == 0)
-            continue;
-        const LaneRuns r = lane_runs(cs[step], ok, any);
-        if ((r.starts >> lane) & 1ull)
-            atomicAdd(&s_pos[w][cs[step]], r.len);
-    }
-    __syncthreads();
-    // counts -> each wave's first position per head
-    for (int k = threadIdx.x; k < num_sites; k += kThreads) {
-        unsigned acc = s_base[k];
-        for (int v = 0; v < kWavesPerBlock; ++v) {
-            const unsigned cnt = s_pos[v][k];
-            s_pos[v][k] = acc;
-            acc += cnt;
+        for (int step = 0; step < kSteps; ++step) {
+            in[step] = FULL || wbase + step * 64 + lane < num_samples;
+            if constexpr (LEVEL)
+                in[step] = in[step] && lv[step] == live.level;
+            if constexpr (MODE == kLevelCell)
+                cs[step] += in[step] ? lv[step] * live.heads : 0u;
         }
-    }
-    __syncthreads();
-    // pass 2: scatter, advancing the wave's positions
+        __syncthreads();
+        // pass 1: this wave's count per head (run leaders)
 #pragma unroll
-    for (int step = 0; step < kSteps; ++step) {
-        const unsigned s = wbase + step * 64 + lane;
-        const bool ok = in[step];
-        const uint64_t any = __ballot(ok);
-        if (LEVEL && any == 0)
-            continue;
-        const unsigned c = cs[step];
-        // each run's leader reserves the run's positions; its lanes follow it
-        const LaneRuns r = lane_runs(c, ok, any);
-        unsigned start = 0;
-        if ((r.starts >> lane) & 1ull)
-            start = atomicAdd(&s_pos[w][c], r.len);
-        start = __shfl(start, r.first);
-        if (ok) {
-            const unsigned pos = start + (unsigned)(lane - r.first);
-            if (pos < num_samples)  // always true when the counts are consistent
-                bucket[pos] = s;
-            if (empty.test(MODE == kLevelCell ? c % live.heads : c))
-                sr[s] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        for (int step = 0; step < kSteps; ++step) {
+            const bool ok = in[step];
+            const uint64_t any = __ballot(ok);
+            if (LEVEL && any == 0)
+                continue;
+            const LaneRuns r = FULL ? lane_runs_full(cs[step]) : lane_runs(cs[step], ok, any);
+            if ((r.starts >> lane) & 1ull)
+                atomicAdd(&s_pos[w][cs[step]], r.len);
         }
-    }
+        __syncthreads();
+        // counts -> each wave's first position per head
+        for (int k = threadIdx.x; k < num_sites; k += kThreads) {
+            unsigned acc = s_base[k];
+            for (int v = 0; v < kWavesPerBlock; ++v) {
+                const unsigned cnt = s_pos[v][k];
+                s_pos[v][k] = acc;
+                acc += cnt;
+            }
+        }
+        __syncthreads();
+        // pass 2: scatter, advancing the wave's positions
+#pragma unroll
+        for (int step = 0; step < kSteps; ++step) {
+            const unsigned s = wbase + step * 64 + lane;
+            const bool ok = in[step];
+            const uint64_t any = __ballot(ok);
+            if (LEVEL && any == 0)
+                continue;
+            const unsigned c = cs[step];
+            // each run's leader reserves the run's positions; its lanes follow it
+            const LaneRuns r = FULL ? lane_runs_full(c) : lane_runs(c, ok, any);
+            unsigned start = 0;
+            if ((r.starts >> lane) & 1ull)
+                start = atomicAdd(&s_pos[w][c], r.len);
+            start = __shfl(start, r.first);
+            if (ok) {
+                const unsigned pos = start + (unsigned)(lane - r.first);
+                if (pos < num_samples)  // always true when the counts are consistent
+                    bucket[pos] = s;
+                if (any_empty && empty.test(MODE == kLevelCell ? c % live.heads : c))
+                    sr[s] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            }
+        }
+    };
+    if (MODE == kCellKey && (unsigned long long)(blockIdx.x + 1) * BLOCK <= num_samples)
+        scatter(std::true_type{});
+    else
+        scatter(std::false_type{});
 }
 
 // After the one-pass (level, head) bucketing: offsets[key] = where key
