@@ -54,7 +54,8 @@ typedef enum {
 } derf_status;
 
 typedef enum {
-    DERF_PREC_FP32 = 0, /* fp32 operands, fp32 MFMA accumulate                      */
+    DERF_PREC_FP32 = 0, /* fp32 operands (carried as two fp16 values each where the  */
+                        /* weights' range allows it, to 23 bits), fp32 accumulate    */
     DERF_PREC_BF16 = 1  /* bf16 operands (round to nearest even), fp32 accumulate   */
 } derf_precision;
 

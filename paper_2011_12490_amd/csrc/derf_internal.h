@@ -14,7 +14,8 @@ constexpr int kBucketBlock = 4096;
 // most of the chip idle there (1,024 rays of 192 samples are 48 blocks), and
 // each block takes four rounds one after another.  Above, 4096 keeps the
 // counts (and their scan) a quarter as long.  196,608 samples of 16 heads:
-// assignment and scatter 15.2 + 9.4 us in blocks of 4096.
+// assignment, scan and scatter 15.2 + 4.8 + 9.4 us in blocks of 4096; 6.0 and,
+// the scan in the scatter, 5.6 us in blocks of 1024.
 constexpr int kSmallBlock = 1024;
 constexpr unsigned kSmallFrame = 1u << 20;
 inline unsigned bucket_block(unsigned num_samples)
@@ -22,8 +23,10 @@ inline unsigned bucket_block(unsigned num_samples)
     return num_samples <= kSmallFrame ? (unsigned)kSmallBlock : (unsigned)kBucketBlock;
 }
 // (head, block) counts up to which the scatter scans them itself, each of its
-// blocks reading all (32 KB); above, by a launch of its own.
-constexpr unsigned long long kScanInScatter = 8192;
+// blocks reading all (20 KB); above, a launch of its own is faster.  us per
+// render, scan launched and in the scatter: 128 counts 27.1, 25.1; 3,072 30.1,
+// 28.7; 4,688 146.7, 143.9; 5,008 35.5, 35.4; 8,192 120.8, 124.3; 32,768 151, 161.
+constexpr unsigned long long kScanInScatter = 5120;
 // Padded length of the per-ray direction feature vector gamma(d / |d|).
 constexpr int kDirPad = 32;
 constexpr int kMaxSites = 256;

@@ -10,13 +10,14 @@
 // Work split.  A workgroup of 4 waves (one per SIMD) takes a tile of one
 // head's samples, NB x 32 per wave, and runs it through the whole network
 // with the activations held in registers.  Two workgroups share a CU (one for
-// width 256, three for bf16 width 64); they do not synchronise with each
+// width 256, three for width 64 but on the fp32 units); they do not synchronise with each
 // other, so one's barriers and gathers are covered by another's matrix work.
 // Workgroups are persistent and take tiles from per-XCD queues, each over a
 // contiguous stretch of tiles (so an XCD's L2 sees few heads), stealing from
 // the other stretches when their own runs out.
 //
-// Operand layout (v_mfma_f32_32x32x16_bf16 / v_mfma_f32_32x32x2_f32):
+// Operand layout (v_mfma_f32_32x32x16_bf16 / _f16 / v_mfma_f32_32x32x2_f32;
+// float32 heads as split fp16 operands, see Split, or on the fp32 units):
 // weights are the A operand (32 output rows x k), samples the B operand
 // (k x 32 samples).  Lane l = n + 32 g holds sample n; a 32x32 result leaves
 // in lane l the 16 rows 8 (i / 4) + 4 g + (i % 4), i = 0..15, and the next

@@ -16,9 +16,9 @@ def _gpu():
     torch.cuda.set_device(0)
 
 
-# 2^20 samples are the last small frame: 1,024 blocks, so 8 heads are the last
-# whose 8,192 counts the scatter scans itself; 40 heads walk their rays
-@pytest.mark.parametrize("heads", [1, 8, 9, 40, 256])
+# 2^20 samples are the last small frame: 1,024 blocks, so 5 heads are the last
+# whose 5,120 counts the scatter scans itself; 40 heads walk their rays
+@pytest.mark.parametrize("heads", [1, 5, 6, 40, 256])
 @pytest.mark.parametrize("rays,n", [(1, 1), (1, 1023), (3, 341), (5, 205), (4099, 7),
                                     (16384, 64), (16385, 64), (33000, 64)])
 def test_blocks_and_scans_agree(heads, rays, n):
