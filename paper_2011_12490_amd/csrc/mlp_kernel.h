@@ -1327,8 +1327,12 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
                 bound = fmaxf(bound, in_max);  // the skip layer's gamma(x) takes the same scale
             if constexpr (l + 1 == C::D)
                 bound = fmaxf(bound, 1.0f);  // and so does gamma(d)
-            const int e = __builtin_amdgcn_frexp_expf(fminf(bound, 0x1p126f));
-            mul = ldexpf(1.0f, ex - e - 14);
+            // Both factors stay finite: an infinite one times an accumulator or
+            // bias of zero would be NaN.  (e < -100: the layer's inputs are all
+            // zero and its biases below 2^-100; e and mul saturate only where
+            // every product is zero or rounds to it.)
+            const int e = max(__builtin_amdgcn_frexp_expf(fminf(bound, 0x1p126f)), -100);
+            mul = ldexpf(1.0f, min(ex - e - 14, 126));
             add = ldexpf(1.0f, 15 - e);
             ex = e;
             top = 0.0f;

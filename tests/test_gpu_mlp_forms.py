@@ -135,3 +135,41 @@ def test_float32_split_ignores_its_neighbours(arch):
     for x, y in zip(a, b):
         assert torch.equal(x[keep], y[keep])
     r.close()
+
+
+@pytest.mark.parametrize("arch", [scenes.ARCH_TINY, scenes.ARCH_SMALL, scenes.ARCH_128],
+                         ids=["4x64", "6x64", "8x128"])
+@pytest.mark.parametrize("kind", ["zero", "zero_last", "far"])
+def test_float32_layers_without_output(arch, kind):
+    """Samples for which every unit of a layer is 0 and the next layer's biases
+    are tiny: the scales stay finite (an infinite one times 0 is NaN), so the
+    outputs are the oracle's, which are what the later layers' biases give.
+    far: the silent layer's inputs are as large as float32 allows."""
+    import oracle
+    from paper_2011_12490_amd import derf
+    n = 33
+    w = scenes.make_weights(arch, 1, 5, 1.0)[0]
+    v = scenes.weight_views(arch, w)
+    at = {"zero": 1, "zero_last": arch.depth - 2, "far": max(arch.skip_layer, 0)}[kind]
+    v["hidden%d" % at][0][:] = 0.0
+    if kind == "far":
+        v["hidden%d" % at][0][:, :3] = -1.0
+    v["hidden%d" % (at + 1)][1][:] = np.float32(1e-12 if kind == "far" else 1e-36)
+    rng = np.random.Generator(np.random.PCG64(7))
+    for l in range(at + 2, arch.depth):
+        v["hidden%d" % l][1][:] = rng.uniform(0.0, 0.1, arch.width)
+    sites = scenes.make_sites("uniform", 1)
+    o, d = _rays(21)
+    if kind == "far":
+        o[::2] = np.float32(3e35)
+    ref = oracle.render(sites, arch, w[None], o, d, 0.0, 1.0, n, 0, seed=6, per_sample=True)
+    r = derf.Renderer(sites, arch, w[None], "fp32")
+    *got, dbg = r.render(torch.from_numpy(o).cuda(), torch.from_numpy(d).cuda(), 0.0, 1.0, n,
+                         seed=6, debug=True)
+    torch.cuda.synchronize()
+    r.close()
+    # float32's rounding: a few units of 2^-24 per layer
+    assert np.abs(dbg["rgb"].cpu().numpy() - ref.srgb).max() <= 1e-5
+    assert np.abs(dbg["sigma"].cpu().numpy() - ref.sigma).max() <= 1e-5 * max(1.0, ref.sigma.max())
+    for x, y in zip(got, (ref.rgb, ref.depth, ref.opacity)):
+        assert np.abs(x.cpu().numpy() - y).max() <= 1e-5
