@@ -321,8 +321,9 @@ struct Cfg {
 
     // per-head resident block: bias of every output tile in accumulator layout;
     // split: then per hidden layer (the colour hidden layer last) the largest
-    // row sum of |W| and the largest |b|, then the output rows' factors
-    static constexpr int SC_OFF = NT * 32, SC_OUT = SC_OFF + 2 * (D + 1);
+    // row sum of |W|, the largest |b| and the exponent that its weights are
+    // stored with (an integer), then the output rows' factors
+    static constexpr int SC_OFF = NT * 32, SC_OUT = SC_OFF + 3 * (D + 1);
     static constexpr int BLOCK_FLOATS = ((SPLIT ? SC_OUT + 4 : NT * 32) + 255) / 256 * 256;
     // the split form's re-encode at the skip layer takes the scale fixed
     // during the layer's second tile
@@ -520,10 +521,16 @@ struct Packer {
 // cycles where the fp32 units take 512.  fp16's exponents are not fp32's, so
 // both operands are kept in its range by powers of two (exact):
 // - weights, here: each hidden unit's row and bias are scaled so that the
-//   row's largest |weight| lies in [1, 2), and the next layers' column of
-//   that unit by the inverse (a ReLU network is unchanged by that); all
-//   weights are then stored times 2^14.  An output row (density, colour) is
-//   scaled alone, its factor kept in the block.
+//   row's largest |weight| has the exponent of its layer's median row, and
+//   the next layers' column of that unit by the inverse (a ReLU network is
+//   unchanged by that); the layer's weights are stored times one power of
+//   two more that takes them to [2^14, 2^15), undone on the accumulators.
+//   (Units brought to [1, 2) each would grow from layer to layer, about 8
+//   times in a Glorot-uniform head of width 64, and leave gamma(x) and
+//   gamma(d), which share their scale, too few bits: 6x64 heads' colours were
+//   off by 1.6e-7 rms, up to 9e-7 for rays of 40 units, with the fp32 units'
+//   at 4.5e-8 and 6.7e-8.)  An output row (density, colour) is scaled alone,
+//   its factor kept in the block.
 // - activations, in the kernel: per sample and layer, by 2^(15 - e), where
 //   2^e exceeds (largest row sum of |W|) (largest |input|) + largest |b|, so
 //   that none exceeds 2^15.  What is lost then is below 2^-40 of that bound.
@@ -541,16 +548,18 @@ struct Split {
     typedef Packer<C> Pk;
     std::vector<float> w;
     std::vector<typename Pk::View> v;
-    float factor[4];  // output rows: true = stored * factor
+    float factor[4];       // output rows: true = stored * factor
+    int shift[C::D + 1];   // hidden layers (the colour hidden layer last): stored = scaled * 2^shift
 
     const float *base;
     bool ok = true;
 
     // 2^e
     static float pow2(int e) { return ldexpf(1.0f, e); }
-    // The power of two 2^-e that takes a row's largest |weight| to [1, 2) (1
-    // for a row of zeros); e outside [-40, 40] does not fit.
-    float row_scale(const float *p, int n)
+    // The exponent e of the power of two that takes a row's largest |weight| to
+    // [1, 2) (kZeroRow for a row of zeros); e outside [-40, 40] does not fit.
+    static constexpr int kZeroRow = 1000;
+    int row_exp(const float *p, int n)
     {
         // (magnitudes compare as integers, which the compiler vectorises)
         unsigned bits = 0;
@@ -563,14 +572,14 @@ struct Split {
         float m;
         memcpy(&m, &bits, 4);
         if (m == 0.0f)
-            return 1.0f;
+            return kZeroRow;
         int x;
         (void)frexpf(m, &x);
         if (x < -39 || x > 41) {
             ok = false;
-            return 1.0f;
+            return 0;
         }
-        return pow2(1 - x);
+        return 1 - x;
     }
     float *at(const float *p) { return w.data() + (p - base); }
     // columns [c0, c0 + col.size()) of a matrix times col, by rows
@@ -585,16 +594,30 @@ struct Split {
         : w(src, views.back().b + views.back().out), v(views), base(src)
     {
         std::vector<float> col;  // what the unit scales leave for the next layer's columns
+        std::vector<int> exps, sorted;
         std::vector<float> mag;  // |biases|
         float typical = 1.0f;    // about the size of a layer's inputs
-        // a layer's rows to [1, 2); col: the inverse scales
-        auto rows = [&](const typename Pk::View &L) {
+        // layer l's rows to their median's size; col: the inverse scales
+        auto rows = [&](const typename Pk::View &L, int l) {
             col.assign(L.out, 1.0f);
             mag.resize(L.out);
+            exps.resize(L.out);
+            sorted.clear();
+            for (int r = 0; r < L.out; ++r) {
+                exps[r] = row_exp(at(L.W) + (size_t)r * L.in, L.in);
+                if (exps[r] != kZeroRow)
+                    sorted.push_back(exps[r]);
+            }
+            int median = 0;
+            if (!sorted.empty()) {
+                std::nth_element(sorted.begin(), sorted.begin() + sorted.size() / 2, sorted.end());
+                median = sorted[sorted.size() / 2];
+            }
+            shift[l] = 14 + median;
             float sq = 0.0f;
             for (int r = 0; r < L.out; ++r) {
                 float *p = at(L.W) + (size_t)r * L.in, *b = at(L.b) + r;
-                const float f = row_scale(p, L.in);
+                const float f = exps[r] == kZeroRow ? 1.0f : pow2(exps[r] - median);
                 *b *= f;
                 mag[r] = fabsf(*b);
                 float part[8] = {};
@@ -618,18 +641,19 @@ struct Split {
         for (int l = 0; l < C::D; ++l) {
             if (l > 0)
                 scale_columns(at(v[l].W), v[l].out, v[l].in, l == C::SKIP ? C::P : 0, col);
-            rows(v[l]);
+            rows(v[l], l);
         }
         scale_columns(at(v[C::D].W), 1, v[C::D].in, 0, col);
         scale_columns(at(v[C::D + 1].W), v[C::D + 1].out, v[C::D + 1].in, 0, col);
         if (C::RH > 0) {
-            rows(v[C::D + 1]);
+            rows(v[C::D + 1], C::D);
             scale_columns(at(v.back().W), 3, v.back().in, 0, col);
         }
         for (int j = 0; j < 4; ++j) {  // density, colour
             const typename Pk::View &L = j ? v.back() : v[C::D];
             float *p = at(L.W) + (size_t)(j ? j - 1 : 0) * L.in;
-            const float f = row_scale(p, L.in);
+            const int x = row_exp(p, L.in);
+            const float f = x == kZeroRow ? 1.0f : pow2(x);
             for (int i = 0; i < L.in; ++i)
                 p[i] *= f;
             factor[j] = 1.0f / f;
@@ -680,6 +704,8 @@ struct Split {
     {
         for (int s = 0; s < C::NS; ++s) {
             const int T = C::st_tile(s), c0 = C::st_c0(s), nu = C::st_units_pad(s);
+            const int kind = C::t_kind(T);
+            const float up = pow2(kind == K_OUT ? 14 : shift[kind == K_HID ? C::t_layer(T) : C::D]);
             unsigned char *out = stream + (size_t)C::st_offset(s) * 1024;
             for (int u = 0; u < nu; u += 2) {  // units u (low halves), u + 1 (high halves)
                 if (u >= C::st_units(s)) {
@@ -691,7 +717,7 @@ struct Split {
                 memcpy(y, x, sizeof(y));
                 unsigned short h[2][512];
                 for (int i = 0; i < 512; ++i)
-                    h[1][i] = to_f16(0x1p14f * y[i], rest[i]);
+                    h[1][i] = to_f16(up * y[i], rest[i]);
                 for (int i = 0; i < 512; ++i) {
                     float none;
                     h[0][i] = to_f16(rest[i], none);
@@ -725,8 +751,9 @@ struct Split {
                 b1 = fabsf(L.b[r]) > b1 ? fabsf(L.b[r]) : b1;
             }
             // (a little above, for the kernel's own rounding of the bound)
-            block[C::SC_OFF + 2 * l] = 1.001f * n1;
-            block[C::SC_OFF + 2 * l + 1] = 1.001f * b1;
+            block[C::SC_OFF + 3 * l] = 1.001f * n1;
+            block[C::SC_OFF + 3 * l + 1] = 1.001f * b1;
+            memcpy(&block[C::SC_OFF + 3 * l + 2], &shift[l], 4);
         }
         for (int j = 0; j < 4; ++j)
             block[C::SC_OUT + j] = factor[j];
@@ -1314,7 +1341,8 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
         // layer), whose inputs are complete
         auto next_scale = [&](auto lc) {
             constexpr int l = decltype(lc)::value;
-            const float n1 = hb[C::SC_OFF + 2 * l], b1 = hb[C::SC_OFF + 2 * l + 1];
+            const float n1 = hb[C::SC_OFF + 3 * l], b1 = hb[C::SC_OFF + 3 * l + 1];
+            const int shift = __float_as_int(hb[C::SC_OFF + 3 * l + 2]);
             float m = l == 0 ? in_max : ldexpf(half_max(top), ex - 15);
             if constexpr (l > 0 && l == C::SKIP)
                 m = fmaxf(m, in_max);
@@ -1332,7 +1360,7 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
             // zero and its biases below 2^-100; e and mul saturate only where
             // every product is zero or rounds to it.)
             const int e = max(__builtin_amdgcn_frexp_expf(fminf(bound, 0x1p126f)), -100);
-            mul = ldexpf(1.0f, min(ex - e - 14, 126));
+            mul = ldexpf(1.0f, min(ex - e - shift, 126));
             add = ldexpf(1.0f, 15 - e);
             ex = e;
             top = 0.0f;
