@@ -534,7 +534,7 @@ struct Packer {
 // - activations, in the kernel: per sample and layer, by 2^(15 - e), where
 //   2^e exceeds (largest row sum of |W|) (largest |input|) + largest |b|, so
 //   that none exceeds 2^15.  What is lost then is below 2^-40 of that bound.
-// Heads whose rows or biases do not fit this (fits()) keep the fp32 units.
+// Heads whose rows or biases do not fit this (fits()) take the fp32 units.
 //
 // Bound by the matrix units (power-limited) with 7 VALU instructions per
 // output value beside them; one accumulator per tile (two, for the small and
@@ -558,6 +558,13 @@ struct Split {
     static float pow2(int e) { return ldexpf(1.0f, e); }
     // The exponent e of the power of two that takes a row's largest |weight| to
     // [1, 2) (kZeroRow for a row of zeros); e outside [-40, 40] does not fit.
+    // Nor does a row most of whose sum can come from weights far below its
+    // largest (read from a unit that is silent, say), which hold fewer bits
+    // than float32: more than a quarter of its weights, but zeros, below 2^-12
+    // of the largest (Glorot-uniform rows reach 2^-4).  One column 2^8 above
+    // the others, which fits: colours of a float32 chain off by 2.4e-7, here
+    // by 1.9e-7 (8x128, the worst of the three); 2^12 2.4e-7 and 2.9e-7, 2^16
+    // 2.4e-7 and 8.6e-7, 2^20 2.4e-7 and 1.1e-5.
     static constexpr int kZeroRow = 1000;
     int row_exp(const float *p, int n)
     {
@@ -573,9 +580,20 @@ struct Split {
         memcpy(&m, &bits, 4);
         if (m == 0.0f)
             return kZeroRow;
+        unsigned least;
+        const float floor = 0x1p-12f * m;
+        memcpy(&least, &floor, 4);
+        int some = 0, small = 0;
+        for (int i = 0; i < n; ++i) {
+            unsigned u;
+            memcpy(&u, p + i, 4);
+            u &= 0x7FFFFFFFu;
+            some += u != 0u;
+            small += u != 0u && u < least;
+        }
         int x;
         (void)frexpf(m, &x);
-        if (x < -39 || x > 41) {
+        if (x < -39 || x > 41 || 4 * small > some) {
             ok = false;
             return 0;
         }

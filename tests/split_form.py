@@ -44,8 +44,15 @@ class Scaled:
         tags = ["hidden%d" % l for l in range(arch.depth)]
         tags += ["rgb_hidden"] if arch.rgb_hidden else []
 
+        self.fits = True  # (the rows' part of the rule)
+
         def exps(m):  # a row's scale to [1, 2), as an exponent
-            return 1 - _frexp(np.abs(m).max(1)), np.abs(m).max(1) > 0
+            u = np.abs(m)
+            top = u.max(1)
+            small = (u > 0) & (u < top[:, None] * F(2.0 ** -12))
+            if (4 * small.sum(1) > (u > 0).sum(1)).any() or (np.abs(1 - _frexp(top)) > 40)[top > 0].any():
+                self.fits = False
+            return 1 - _frexp(top), top > 0
 
         self.shift = {"sigma": 14, "rgb_out": 14}
         last = "rgb_hidden" if arch.rgb_hidden else "rgb_out"
