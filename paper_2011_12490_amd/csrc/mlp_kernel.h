@@ -580,6 +580,10 @@ struct Split {
         memcpy(&m, &bits, 4);
         if (m == 0.0f)
             return kZeroRow;
+        if (bits >= 0x7F800000u) {  // the unit scales took a weight out of float32's range
+            ok = false;
+            return 0;
+        }
         unsigned least;
         const float floor = 0x1p-12f * m;
         memcpy(&least, &floor, 4);

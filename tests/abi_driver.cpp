@@ -3,6 +3,7 @@
 // on the host side only -- device code is never instrumented):
 //   * every argument check and early-failure path that needs no GPU, including
 //     derf_create's clean-up of a handle whose device setup fails;
+//   * which float32 heads take the split form, and which the fp32 units;
 //   * allocation failures: each allocation of derf_create, derf_create_mixed,
 //     the render workspace and derf_set_gate is made to fail in turn
 //     (derf_debug_fail_alloc); each must return DERF_ERR_OOM, hand out no
@@ -20,6 +21,7 @@
 #include <hip/hip_runtime.h>
 
 #include "derf.h"
+#include "derf_internal.h"
 
 // exported by fault-injection builds of the library only
 extern "C" void derf_debug_fail_alloc(long n);
@@ -177,6 +179,59 @@ static void fault_injection()
     printf("fault injection: render workspace, gate and stored-encoding failures handled\n");
 }
 
+// 4x64 float32 heads, changed in one place each, that the split form takes or
+// leaves to the fp32 units.
+static void head_forms()
+{
+    const derf::MlpVariant *v = derf::find_mlp_variant({6, 4, 4, 64, -1, 0}, false);
+    expect(v && v->plain && v->fits && !v->plain->fits && !v->plain->plain,
+           "float32 heads have a form for all weights beside the split one");
+    if (!v || !v->fits)
+        return;
+    const Frame f;  // (its first head)
+    const derf_head_arch tiny = {6, 4, 4, 64, -1, 0};
+    const std::vector<float> plain(f.weights.begin(), f.weights.begin() + derf_weights_count(&tiny));
+    constexpr int P = 39, W = 64, kLayer0 = W * P + W, kLayer = W * W + W;
+    const int hidden1 = kLayer0, hidden3 = kLayer0 + 2 * kLayer, sigma = kLayer0 + 3 * kLayer;
+    auto fits = [&](auto change) {
+        std::vector<float> w = plain;
+        change(w.data());
+        return v->fits(w.data());
+    };
+    expect(fits([](float *) {}), "ordinary weights take the split form");
+    expect(fits([&](float *w) { memset(w + hidden1 + 5 * W, 0, W * sizeof(float)); }),
+           "a row of zeros does");
+    expect(fits([&](float *w) { memset(w, 0, plain.size() * sizeof(float)); }), "all zeros do");
+    auto row = [&](float *w, int at, float by) {
+        for (int i = 0; i < W; ++i)
+            w[at + i] *= by;
+    };
+    expect(fits([&](float *w) {
+               row(w, hidden1 + 5 * W, 0x1p30f);
+               for (int i = 0; i < W; ++i)
+                   w[hidden1 + kLayer + i * W + 5] *= 0x1p-30f;
+           }),
+           "a unit scaled by 2^30, and back where it is read, does");
+    expect(!fits([&](float *w) { row(w, hidden1 + 5 * W, 0x1p60f); }), "a row of 2^60 does not");
+    expect(!fits([&](float *w) { row(w, hidden1 + 5 * W, 0x1p-60f); }), "a row of 2^-60 does not");
+    expect(!fits([&](float *w) { w[hidden1 + W * W + 5] = 1e6f; }),
+           "a bias far above its layer does not");
+    expect(!fits([&](float *w) { w[hidden1 + 5 * W + 7] = 1e6f; }),
+           "a weight far above its row does not");
+    // unit 5 of the last layer is never on, its row's scale takes the one
+    // weight that reads it out of float32's range
+    expect(!fits([&](float *w) {
+               for (int i = 0; i < W; ++i)
+                   w[hidden3 + 5 * W + i] = -0x1p39f * (1.0f + i / 64.0f);
+               w[hidden3 + W * W + 5] = 0.0f;
+               memset(w + sigma, 0, W * sizeof(float));
+               w[sigma + 5] = 0x1p100f;
+               for (int c = 0; c < 3; ++c)  // (no colour reads it)
+                   w[sigma + W + 1 + c * (W + 27) + 5] = 0.0f;
+           }),
+           "an output weight that the unit scales overflow does not");
+}
+
 int main()
 {
     const derf_head_arch tiny = {6, 4, 4, 64, -1, 0};
@@ -268,6 +323,7 @@ int main()
     expect(derf_create(&h, K, sites.data(), &weird, weights.data(), 1) == DERF_ERR_UNSUPPORTED,
            "create with a very wide head");
     expect(strlen(derf_last_error()) < 512, "error text fits its buffer");
+    head_forms();
     fault_injection();
     printf("abi driver: %d failure(s)\n", failures);
     return failures == 0 ? 0 : 1;
