@@ -147,6 +147,16 @@ int derf_create(derf_handle **out, int num_sites, const float *sites_xyz,
 int derf_create_mixed(derf_handle **out, int num_sites, const float *sites_xyz,
                       const derf_head_arch *archs, const float *weights, int precision);
 
+/* The operands that head `head` of a renderer is evaluated with: one form per
+ * architecture, chosen when the renderer is created.  DERF_PREC_FP32 heads
+ * take DERF_ARITH_SPLIT (each operand carried as two fp16 values, products on
+ * the fp16 matrix units) if the weights of every head of their architecture
+ * keep float32's precision that way, else DERF_ARITH_FP32 (the fp32 matrix
+ * units, about a third of the speed).  DERF_ERR_INVALID_ARG for a NULL handle
+ * or a head out of range. */
+enum { DERF_ARITH_FP32 = 0, DERF_ARITH_BF16 = 1, DERF_ARITH_SPLIT = 2 };
+int derf_head_arithmetic(const derf_handle *h, int head);
+
 /* Render num_rays rays.  All array arguments are device pointers:
  *   rays_o, rays_d   float [R][3] origins and directions (directions need
  *                    not be unit length: samples are o + t d, the colour

@@ -1179,6 +1179,21 @@ int derf_create_mixed(derf_handle **out, int num_sites, const float *sites_xyz,
     return create_impl(out, num_sites, sites_xyz, archs, true, weights, precision);
 }
 
+int derf_head_arithmetic(const derf_handle *h, int head)
+{
+    if (!h)
+        return fail(DERF_ERR_INVALID_ARG, "null handle");
+    if (head < 0 || head >= h->num_sites)
+        return fail(DERF_ERR_INVALID_ARG, "head %d of %d", head, h->num_sites);
+    if (h->bf16)
+        return DERF_ARITH_BF16;
+    for (int gi = 0; gi < h->num_groups; ++gi)
+        if (h->groups[gi].members.test(head))
+            // (only the split form leaves some weights to another)
+            return h->groups[gi].mlp->plain ? DERF_ARITH_SPLIT : DERF_ARITH_FP32;
+    return fail(DERF_ERR_INVALID_ARG, "head %d has no group", head);
+}
+
 int derf_render(derf_handle *h, const float *rays_o, const float *rays_d, long long num_rays,
                 float near_t, float far_t, const derf_sampling *samp, float *out_rgb,
                 float *out_depth, float *out_opacity, void *hip_stream)

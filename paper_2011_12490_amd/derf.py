@@ -54,7 +54,7 @@ class derf_stats(ctypes.Structure):
                 ("walk_rays", ctypes.c_longlong), ("walk_fallback_rays", ctypes.c_longlong)]
 
 
-EXPORTS = ("derf_weights_count", "derf_create", "derf_create_mixed", "derf_render",
+EXPORTS = ("derf_weights_count", "derf_create", "derf_create_mixed", "derf_head_arithmetic", "derf_render",
            "derf_render_debug", "derf_render_noalloc",
            "derf_render_soft", "derf_render_culled", "derf_set_empty_heads", "derf_set_gate",
            "derf_gate_weights_count", "derf_render_gated", "derf_set_encoding", "derf_set_timing",
@@ -88,6 +88,8 @@ def lib() -> ctypes.CDLL:
         L.derf_create.restype = ctypes.c_int
         L.derf_create_mixed.argtypes = L.derf_create.argtypes
         L.derf_create_mixed.restype = ctypes.c_int
+        L.derf_head_arithmetic.argtypes = [P, ctypes.c_int]
+        L.derf_head_arithmetic.restype = ctypes.c_int
         render_args = [P, P, P, ctypes.c_longlong, ctypes.c_float, ctypes.c_float,
                        ctypes.POINTER(derf_sampling), P, P, P]
         L.derf_render.argtypes = render_args + [P]
@@ -241,6 +243,18 @@ def derf_create(sites, arch, weights, precision: int) -> ctypes.c_void_p:
                              ctypes.byref(a), w.ctypes.data_as(ctypes.c_void_p), precision),
            "derf_create")
     return h
+
+
+DERF_ARITH_FP32 = 0
+DERF_ARITH_BF16 = 1
+DERF_ARITH_SPLIT = 2
+
+
+def derf_head_arithmetic(h, head: int) -> int:
+    """The operands that a head is evaluated with (DERF_ARITH_*)."""
+    form = lib().derf_head_arithmetic(h, head)
+    _check(min(form, DERF_OK), "derf_head_arithmetic")
+    return form
 
 
 def derf_render(h, rays_o: torch.Tensor, rays_d: torch.Tensor, near: float, far: float,
