@@ -279,9 +279,9 @@ __device__ __forceinline__ unsigned group_exclusive_sum(unsigned x, int gl)
 // its smaller end; between the largest such fractions at both ends c alone
 // can be nearest, and the lookup takes it without looking at the sites (the
 // fraction is rounded up to a power of two, kept in four bits).  A ray with more than
-// kMaxSeg segments, a segment with more than kMaxCand candidates or
-// coordinates beyond float32's squares is marked (nseg = 0) for the search
-// over all sites.
+// kMaxSeg segments, a segment with more than kMaxCand candidates, or
+// coordinates or distances beyond float32's squares is marked (nseg = 0) for
+// the search over all sites.
 //
 // One lane per ray (the largest frames) asks for 7 waves per SIMD: 72
 // registers without spills, against 5 waves by default, to cover the lanes'
@@ -369,6 +369,11 @@ void ray_walk_kernel(RenderGeometry g, const float4 *__restrict__ sites, int num
         const double qc1 = q(x1, y1, z1, c);
         const double dc0 = fma(x0, x0, fma(y0, y0, z0 * z0)) + qc0;
         const double dc1 = fma(x1, x1, fma(y1, y1, z1 * z1)) + qc1;
+        // (nor has one whose nearest site is out of that range)
+        if (!(fmax(dc0, dc1) < 1e36)) {
+            ok = false;
+            break;
+        }
         const double tau = 1e-4 * (1.0 + fmax(dc0, dc1));
         // this lane's candidates but c, ascending, as a byte string (at most
         // 12 kept), and the largest fraction that one of them is near on

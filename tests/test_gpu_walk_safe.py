@@ -61,3 +61,32 @@ def test_safe_stretches_give_the_searched_cells(layout, k, rays, n, near, far):
     want = oracle.assign_depths(sites, o, d, t, nthreads=min(16, os.cpu_count() or 1))
     want = want[0] if isinstance(want, tuple) else want
     assert np.array_equal(cell, want)
+
+
+@pytest.mark.parametrize("k,rays", [(17, 60), (40, 60), (23, 1 << 18), (23, 1 << 19)])
+@pytest.mark.parametrize("layout", ["all_far", "some_far", "far_apart"])
+def test_sites_beyond_float32_squares(layout, k, rays):
+    """Sites whose squared distances overflow float32: with no finite distance
+    the search takes the first site, and a ray's walk must not say otherwise."""
+    from paper_2011_12490_amd import derf
+    rng = np.random.Generator(np.random.PCG64(k + rays))
+    sites = rng.uniform(-1.0, 1.0, (k, 3)).astype(np.float32)
+    far = (np.sign(sites) * np.float32(2e19) + sites * np.float32(1e20)).astype(np.float32)
+    if layout == "all_far":
+        sites = far
+    elif layout == "some_far":
+        sites[::2] = far[::2]
+    else:  # every distance is finite
+        sites *= np.float32(1e18)
+    o = rng.uniform(-1.0, 1.0, (rays, 3)).astype(np.float32)
+    d = rng.uniform(-1.0, 1.0, (rays, 3)).astype(np.float32)
+    o[1] = np.float32(5e17)
+    r = derf.Renderer(sites, scenes.ARCH_TINY, scenes.make_weights(scenes.ARCH_TINY, k), "bf16")
+    dbg = r.render(torch.from_numpy(o).cuda(), torch.from_numpy(d).cuda(), 0.0, 1.0, 5, seed=4,
+                   debug=True)[3]
+    torch.cuda.synchronize()
+    t, cell = dbg["t"].cpu().numpy(), dbg["cell"].cpu().numpy()
+    r.close()
+    want = oracle.assign_depths(sites, o, d, t, nthreads=min(16, os.cpu_count() or 1))
+    want = want[0] if isinstance(want, tuple) else want
+    assert np.array_equal(cell, want)
