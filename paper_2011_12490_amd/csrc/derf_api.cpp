@@ -220,8 +220,9 @@ struct Buffers {
     void *gxtab;                 // [max(S, Sf)] rows of gx_bytes (stored encoding), or null
 };
 
+// walks: the render may walk its rays (a gated one never does)
 size_t layout(char *base, unsigned S, unsigned Sf, unsigned R, unsigned nblk, int K, bool bf16,
-              size_t gx_bytes, Buffers *b)
+              size_t gx_bytes, Buffers *b, bool walks = true)
 {
     char *p = base;
     Buffers x;
@@ -237,7 +238,7 @@ size_t layout(char *base, unsigned S, unsigned Sf, unsigned R, unsigned nblk, in
     x.totals = carve<unsigned>(p, K);
     x.totals_fine = carve<unsigned>(p, K);
     x.mlp_queue = carve<unsigned>(p, kMlpQueues * kMaxHeadGroups);
-    const bool walk = K >= kWalkSites;
+    const bool walk = walks && K >= kWalkSites;
     x.walk_seg = walk ? carve<SegRec>(p, (size_t)R * kMaxSeg) : nullptr;
     x.walk_nseg = walk ? carve<unsigned char>(p, R) : nullptr;
     x.gxtab = gx_bytes ? carve<char>(p, (size_t)(S > Sf ? S : Sf) * gx_bytes) : nullptr;
@@ -932,7 +933,7 @@ int render_gated_impl(derf_handle *h, const float *rays_o, const float *rays_d,
     const unsigned R = (unsigned)num_rays, N = (unsigned)samp->n_coarse, S = R * N;
     const unsigned block = bucket_block(S), nblk = blocks_of(S, block);
     const int K = h->num_sites;
-    int rc = ensure_workspace(h, layout(nullptr, S, 0, R, nblk, K, h->bf16, 0, nullptr));
+    int rc = ensure_workspace(h, layout(nullptr, S, 0, R, nblk, K, h->bf16, 0, nullptr, false));
     if (rc != DERF_OK)
         return rc;
     if (h->timing && h->ev_pending) {
@@ -940,7 +941,7 @@ int render_gated_impl(derf_handle *h, const float *rays_o, const float *rays_d,
         accumulate_timing(h);
     }
     Buffers b;
-    layout(reinterpret_cast<char *>(h->ws.mem), S, 0, R, nblk, K, h->bf16, 0, &b);
+    layout(reinterpret_cast<char *>(h->ws.mem), S, 0, R, nblk, K, h->bf16, 0, &b, false);
 
     RenderGeometry g;
     g.rays_o = rays_o;

@@ -182,3 +182,25 @@ def test_gated_errors_and_gate_removal():
         r.render_gated(o, d, cfg.near, cfg.far, cfg.n_coarse)
     torch.cuda.synchronize()
     r.close()
+
+
+def test_gated_workspace_holds_no_walk_tables():
+    """A gated render walks no rays: from 17 heads on its workspace is that of
+    its samples and rays (25 bytes a sample, 64 a ray, and an eighth to grow
+    by), without the 513 bytes a ray of the walk tables."""
+    from paper_2011_12490_amd import derf
+    K, R, n = 17, 1 << 20, 2
+    r = derf.Renderer(scenes.make_sites("uniform", K), scenes.ARCH_TINY,
+                      scenes.make_weights(scenes.ARCH_TINY, K), "bf16")
+    rng = np.random.Generator(np.random.PCG64(1))
+    r.set_gate(6, 16, rng.uniform(-1.0, 1.0, 16 * 39 + 16 + K * 17).astype(np.float32))
+    o, d = torch.rand((R, 3), device="cuda"), torch.rand((R, 3), device="cuda")
+    r.render_gated(o[:8], d[:8], 0.0, 1.0, n)
+    out = [torch.empty(s, device="cuda") for s in ((R, 3), (R,), (R,))]
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    derf.derf_render_gated(r.handle, o, d, 0.0, 1.0, derf.derf_sampling(n, 0, 1, 1, 0), *out)
+    torch.cuda.synchronize()
+    used = free - torch.cuda.mem_get_info()[0]
+    r.close()
+    assert used <= 1.2 * R * (25 * n + 64) + (4 << 20)
