@@ -24,6 +24,20 @@ struct CullLevel {
     float eps;
 };
 constexpr int kMaxLevels = 32;
+
+// f(i) for thread `thread` of block `block`'s share of `count` words.  In 64
+// bits: a grid may hold 2^32 - 1 threads, and a 32-bit step that wraps walks
+// the words below it again (a grid of 2^24 - 1 blocks of 256: up to 2^20 times
+// at 2^28 counts).
+template <class F>
+__host__ __device__ inline void each_word(unsigned count, unsigned block, unsigned thread,
+                                          unsigned blocks, unsigned threads, F f)
+{
+    const unsigned long long step = (unsigned long long)blocks * threads;
+    for (unsigned long long i = (unsigned long long)block * threads + thread; i < count; i += step)
+        f((size_t)i);
+}
+
 // clear, clear_count (here and at launch_level_composite): words to set to
 // zero for a later kernel, or null, 0
 hipError_t launch_level_bounds(const uint8_t *cell, unsigned n, unsigned num_rays,

@@ -929,8 +929,8 @@ struct ClearWords {
     unsigned count;
     __device__ __forceinline__ void run() const
     {
-        for (unsigned i = blockIdx.x * kThreads + threadIdx.x; i < count; i += gridDim.x * kThreads)
-            p[i] = 0;
+        each_word(count, blockIdx.x, threadIdx.x, gridDim.x, kThreads,
+                  [this](size_t i) { p[i] = 0; });
     }
 };
 

@@ -21,6 +21,7 @@
 #include <hip/hip_runtime.h>
 
 #include "derf.h"
+#include "derf_cull.h"
 #include "derf_internal.h"
 
 // exported by fault-injection builds of the library only
@@ -232,6 +233,28 @@ static void head_forms()
            "an output weight that the unit scales overflow does not");
 }
 
+// Every word of a clear is taken once, by grids up to the largest.
+static void clear_steps()
+{
+    const unsigned grids[] = {1, 3, 4096, (1u << 24) - 100, (1u << 24) - 1};
+    for (const unsigned blocks : grids)
+        for (const unsigned count : {0u, 1u, 257u, 1u << 20}) {
+            std::vector<unsigned char> taken(count, 0);
+            unsigned long long visits = 0;
+            // (blocks past the words do nothing: the last one is enough of them)
+            for (unsigned b = 0; b < blocks; b = b == 5000 ? blocks - 1 : b + 1)
+                for (unsigned t = 0; t < 256; ++t)
+                    derf::each_word(count, b, t, blocks, 256, [&](size_t i) {
+                        ++visits;
+                        taken.at(i) = 1;
+                    });
+            bool all = true;
+            for (const unsigned char x : taken)
+                all = all && x;
+            expect(all && visits == count, "each word of a clear is taken once");
+        }
+}
+
 int main()
 {
     const derf_head_arch tiny = {6, 4, 4, 64, -1, 0};
@@ -324,6 +347,7 @@ int main()
            "create with a very wide head");
     expect(strlen(derf_last_error()) < 512, "error text fits its buffer");
     head_forms();
+    clear_steps();
     fault_injection();
     printf("abi driver: %d failure(s)\n", failures);
     return failures == 0 ? 0 : 1;
