@@ -66,6 +66,8 @@ __device__ __forceinline__ float site_distance(const float4 &p, float x, float y
 // at 64 heads.
 constexpr int kStageHeads = 64;
 constexpr int kRow = 65;
+// the static arrays' bytes at most (sites, positions or one row of them, coefficients)
+constexpr size_t kStaticLds = kMaxSites * sizeof(float4) + 64 * sizeof(float4) + kWaves * 64 * sizeof(float);
 // sr loads in flight per lane
 constexpr int kBatch = 8;
 
@@ -259,9 +261,10 @@ hipError_t launch_soft_composite(const RenderGeometry &g, const float4 *sites, i
     const bool stage = num_sites <= kStageHeads;
     const size_t lds = stage ? (size_t)kWaves * num_sites * kRow * sizeof(float) : 0;
     auto go = [&](auto kernel) {
-        // more than 64 KB of LDS (63 heads on) has to be allowed, where the
-        // runtime keeps that limit; the launch reports any real problem
-        if (lds > 0xF000 && hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+        // more than 64 KB of LDS (58 heads on, with the 6 KB of the static
+        // arrays) has to be allowed, where the runtime keeps that limit; the
+        // launch reports any real problem
+        if (lds + kStaticLds > 0x10000 && hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
                                                 (int)lds) != hipSuccess)
             (void)hipGetLastError();
