@@ -54,8 +54,9 @@ typedef enum {
 } derf_status;
 
 typedef enum {
-    DERF_PREC_FP32 = 0, /* fp32 operands (carried as two fp16 values each where the  */
-                        /* weights' range allows it, to 23 bits), fp32 accumulate    */
+    DERF_PREC_FP32 = 0, /* fp32 operands (carried as two fp16 values each, to 23     */
+                        /* bits, for weights that allow it: derf_head_arithmetic),   */
+                        /* fp32 accumulate                                           */
     DERF_PREC_BF16 = 1  /* bf16 operands (round to nearest even), fp32 accumulate   */
 } derf_precision;
 
@@ -344,13 +345,16 @@ int derf_set_encoding(derf_handle *h, int mode);
  * walk_rays and walk_fallback_rays describe the last render's assignment
  * (Sec. 3.3: a ray crosses each convex cell in one segment): from 17 heads
  * every ray is first walked through its cells; a ray that crosses more than
- * 32 cells, or has a segment with more than 11 near-tied candidate sites, is
- * assigned by the search over all sites instead (same cells, more work).
+ * 32 cells, has a segment with more than 11 near-tied candidate sites, or
+ * coordinates or distances to the sites beyond 1e18, is assigned by the search
+ * over all sites instead (same cells, more work).
  * walk_rays is 0 when the render searched all sites for every sample. */
 enum {
     DERF_STAGE_SAMPLE = 0,         /* sample + encode + assign (given depths: assign);
                                       the stored gamma(x) pass                        */
-    DERF_STAGE_BUCKET_SCAN = 1,    /* per-head counts -> offsets                     */
+    DERF_STAGE_BUCKET_SCAN = 1,    /* per-head counts -> offsets (an empty interval
+                                      where the scatter scans them itself: up to
+                                      5,120 counts, a block's count of each head)     */
     DERF_STAGE_BUCKET_SCATTER = 2, /* sample ids into per-head buckets               */
     DERF_STAGE_MLP = 3,            /* grouped per-head MLP                           */
     DERF_STAGE_COMPOSITE = 4,      /* segment integration + Painter's merge          */

@@ -15,7 +15,16 @@ constexpr int kBucketBlock = 4096;
 // each block takes four rounds one after another.  Above, 4096 keeps the
 // counts (and their scan) a quarter as long.  196,608 samples of 16 heads:
 // assignment, scan and scatter 15.2 + 4.8 + 9.4 us in blocks of 4096; 6.0 and,
-// the scan in the scatter, 5.6 us in blocks of 1024.
+// the scan in the scatter, 5.6 us in blocks of 1024.  Whole renders through
+// 4x64 bf16 heads, us in blocks of 4096 and of 1024:
+//   samples   1 head        16 heads      64 heads      256 heads
+//   131,072   29.6,  23.5   37.6,  26.7   82.0,  67.0   177.8, 161.3
+//   1 << 20   124.0, 122.0  131.0, 124.0  177.0, 163.8  301.7, 288.4
+//   1 << 21   176.2, 178.8  184.5, 178.4  230.0, 217.4  364.2, 353.9
+//   1 << 22   285.7, 310.8  299.0, 290.3  339.9, 332.4  486.0, 480.0
+// so the line lies where 1024 is the faster one for every number of heads.
+// (The culled render keeps 4096 at every size: its level kernels are built for
+// that partition alone, and the smaller one has not been measured there.)
 constexpr int kSmallBlock = 1024;
 constexpr unsigned kSmallFrame = 1u << 20;
 inline unsigned bucket_block(unsigned num_samples)

@@ -1195,9 +1195,9 @@ __global__ __launch_bounds__(kThreads) void level_ray_scatter_kernel(
 // Stable scatter of sample ids into per-head buckets.  Bucket k occupies
 // [offset_k, offset_k + total_k) with offset_k = sum of totals below k;
 // within it samples keep increasing sample-id order, so each ray's run
-// through cell k stays contiguous.  Block b's samples are its 4096 of the
-// counting pass; wave w takes the 1024 consecutive ones from 1024 w, in 16
-// steps of 64 (all 16 cells loaded up front, four to a lane: wave_bytes).
+// through cell k stays contiguous.  Block b's samples are its BLOCK of the
+// counting pass; wave w takes a quarter of them, consecutive ones, in kSteps
+// steps of 64 (all their cells loaded up front, four to a lane: wave_bytes).
 // Pass 1 counts each wave's samples per head (equal-cell runs, wave-private
 // counters); after one
 // barrier every wave knows its first position per head (the block's base

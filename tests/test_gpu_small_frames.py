@@ -50,37 +50,45 @@ def test_blocks_and_scans_agree(heads, rays, n):
 
 
 def test_noalloc_takes_the_same_frames():
-    """256 heads at the largest frame the scratch holds in blocks of 4096: its
-    longer counts would not fit, and it is rendered all the same."""
+    """The largest frame that the scratch array holds with its counts in blocks
+    of 4096, though it is a small one (below 2^20 samples) whose counts in
+    blocks of 1024 no longer fit: it is rendered all the same, as derf_render
+    does.  256 heads take so many rays less than 17 as their counts in blocks
+    of 4096 need, not the fourfold ones of blocks of 1024."""
     from paper_2011_12490_amd import derf
-    heads, n = 256, 192
+    n, most = 8, 1 << 17
     rng = np.random.Generator(np.random.PCG64(1))
-    sites = rng.uniform(-1.0, 1.0, (heads, 3)).astype(np.float32)
-    r = derf.Renderer(sites, scenes.ARCH_TINY, scenes.make_weights(scenes.ARCH_TINY, heads), "bf16")
-    out = [torch.empty(s, device="cuda") for s in ((8192 * 2, 3), (8192 * 2,), (8192 * 2,))]
+    o = torch.from_numpy(rng.uniform(-1.0, 1.0, (most, 3)).astype(np.float32)).cuda()
+    out = [torch.empty(s, device="cuda") for s in ((most, 3), (most,), (most,))]
+    samp = derf.derf_sampling(n, 0, 1, 1, 0)
+    limit = {}
+    for heads in (17, 256):
+        sites = rng.uniform(-1.0, 1.0, (heads, 3)).astype(np.float32)
+        r = derf.Renderer(sites, scenes.ARCH_TINY, scenes.make_weights(scenes.ARCH_TINY, heads),
+                          "bf16")
 
-    def takes(rays):
-        o = torch.from_numpy(rng.uniform(-1.0, 1.0, (rays, 3)).astype(np.float32)).cuda()
-        try:
-            derf.derf_render_noalloc(r.handle, o, o, 0.0, 1.0, derf.derf_sampling(n, 0, 1, 1, 0), *out)
-        except derf.DerfError as e:
-            assert e.status == derf.DERF_ERR_INVALID_ARG
-            return False
+        def takes(rays):
+            try:
+                derf.derf_render_noalloc(r.handle, o[:rays], o[:rays], 0.0, 1.0, samp, *out)
+            except derf.DerfError as e:
+                assert e.status == derf.DERF_ERR_INVALID_ARG
+                return False
+            torch.cuda.synchronize()
+            return True
+
+        lo, hi = 1, most
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            lo, hi = (mid, hi) if takes(mid) else (lo, mid)
+        limit[heads] = lo
+        assert takes(lo)
+        want = r.render(o[:lo], o[:lo], 0.0, 1.0, n, seed=1)
         torch.cuda.synchronize()
-        return True
-
-    lo, hi = 1, 8192 * 2
-    while hi - lo > 1:
-        mid = (lo + hi) // 2
-        lo, hi = (mid, hi) if takes(mid) else (lo, mid)
-
-    # the workspace in blocks of 4096, as the library lays it out
-    def need(rays):
-        s = rays * n
-        nblk = -(-s // 4096)
-        up = lambda b: -(-b // 256) * 256
-        return sum(up(b) for b in (4 * s, s + 16, 16 * s, 0, 0, 0, 4 * s, rays * 64,
-                                   4 * nblk * heads, 4 * heads, 4 * heads, 128, rays * 512, rays))
-
-    assert need(lo) <= derf.DERF_NOALLOC_SCRATCH_BYTES < need(hi)
-    r.close()
+        for x, y in zip(out, want):
+            assert torch.equal(x[:lo], y)
+        r.close()
+    samples = limit[256] * n
+    assert samples < 1 << 20
+    counts = (256 - 17) * 4 * -(-samples // 4096)
+    per_ray = derf.DERF_NOALLOC_SCRATCH_BYTES / limit[17]
+    assert 0 < (limit[17] - limit[256]) * per_ray < 1.5 * counts
