@@ -321,9 +321,9 @@ struct Cfg {
 
     // per-head resident block: bias of every output tile in accumulator layout;
     // split: then per hidden layer (the colour hidden layer last) the largest
-    // row sum of |W|, the largest |b| and the exponent that its weights are
-    // stored with (an integer), then the output rows' factors
-    static constexpr int SC_OFF = NT * 32, SC_OUT = SC_OFF + 3 * (D + 1);
+    // row sum of |W|, the largest |b| and the inverse of the power of two that
+    // its weights are stored with, in 16 bytes, then the output rows' factors
+    static constexpr int SC_OFF = NT * 32, SC_OUT = SC_OFF + 4 * (D + 1);
     static constexpr int BLOCK_FLOATS = ((SPLIT ? SC_OUT + 4 : NT * 32) + 255) / 256 * 256;
     // the split form's re-encode at the skip layer takes the scale fixed
     // during the layer's second tile
@@ -552,6 +552,7 @@ struct Split {
     int shift[C::D + 1];   // hidden layers (the colour hidden layer last): stored = scaled * 2^shift
 
     const float *base;
+    const bool check;  // whether ok is wanted
     bool ok = true;
 
     // 2^e
@@ -586,20 +587,24 @@ struct Split {
             ok = false;
             return 0;
         }
-        unsigned least;
-        const float floor = 0x1p-12f * m;
-        memcpy(&least, &floor, 4);
-        int some = 0, small = 0;
-        for (int i = 0; i < n; ++i) {
-            unsigned u;
-            memcpy(&u, p + i, 4);
-            u &= 0x7FFFFFFFu;
-            some += u != 0u;
-            small += u != 0u && u < least;
+        if (check) {
+            unsigned least;
+            const float floor = 0x1p-12f * m;
+            memcpy(&least, &floor, 4);
+            int small = 0, some = 0;
+            for (int i = 0; i < n; ++i) {
+                unsigned u;
+                memcpy(&u, p + i, 4);
+                small += (u & 0x7FFFFFFFu) - 1u < least - 1u;  // (zeros are none)
+            }
+            for (int i = 0; small > 0 && i < n; ++i)
+                some += p[i] != 0.0f;
+            if (4 * small > some)
+                ok = false;
         }
         int x;
         (void)frexpf(m, &x);
-        if (x < -39 || x > 41 || 4 * small > some) {
+        if (x < -39 || x > 41) {
             ok = false;
             return 0;
         }
@@ -614,8 +619,8 @@ struct Split {
                 p[(size_t)r * in + c0 + i] *= col[i];
     }
 
-    Split(const float *src, const std::vector<typename Pk::View> &views)
-        : w(src, views.back().b + views.back().out), v(views), base(src)
+    Split(const float *src, const std::vector<typename Pk::View> &views, bool check_fits = false)
+        : w(src, views.back().b + views.back().out), v(views), base(src), check(check_fits)
     {
         std::vector<float> col;  // what the unit scales leave for the next layer's columns
         std::vector<int> exps, sorted;
@@ -695,7 +700,7 @@ struct Split {
     {
         std::vector<typename Pk::View> v;
         Pk::views(src, v);
-        return Split(src, v).ok;
+        return Split(src, v, true).ok;
     }
 
     // x (|x| < 65504) to fp16, nearest even, and what is left of it.  In
@@ -777,9 +782,9 @@ struct Split {
                 b1 = fabsf(L.b[r]) > b1 ? fabsf(L.b[r]) : b1;
             }
             // (a little above, for the kernel's own rounding of the bound)
-            block[C::SC_OFF + 3 * l] = 1.001f * n1;
-            block[C::SC_OFF + 3 * l + 1] = 1.001f * b1;
-            memcpy(&block[C::SC_OFF + 3 * l + 2], &shift[l], 4);
+            block[C::SC_OFF + 4 * l] = 1.001f * n1;
+            block[C::SC_OFF + 4 * l + 1] = 1.001f * b1;
+            block[C::SC_OFF + 4 * l + 2] = pow2(-shift[l]);
         }
         for (int j = 0; j < 4; ++j)
             block[C::SC_OUT + j] = factor[j];
@@ -1367,8 +1372,8 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
         // layer), whose inputs are complete
         auto next_scale = [&](auto lc) {
             constexpr int l = decltype(lc)::value;
-            const float n1 = hb[C::SC_OFF + 3 * l], b1 = hb[C::SC_OFF + 3 * l + 1];
-            const int shift = __float_as_int(hb[C::SC_OFF + 3 * l + 2]);
+            const f32x4 sc = *reinterpret_cast<const f32x4 *>(hb + C::SC_OFF + 4 * l);
+            const float n1 = sc[0], b1 = sc[1];
             float m = l == 0 ? in_max : ldexpf(half_max(top), ex - 15);
             if constexpr (l > 0 && l == C::SKIP)
                 m = fmaxf(m, in_max);
@@ -1382,11 +1387,11 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void mlp_kernel(
             if constexpr (l + 1 == C::D)
                 bound = fmaxf(bound, 1.0f);  // and so does gamma(d)
             // Both factors stay finite: an infinite one times an accumulator or
-            // bias of zero would be NaN.  (e < -100: the layer's inputs are all
-            // zero and its biases below 2^-100; e and mul saturate only where
-            // every product is zero or rounds to it.)
-            const int e = max(__builtin_amdgcn_frexp_expf(fminf(bound, 0x1p126f)), -100);
-            mul = ldexpf(1.0f, min(ex - e - shift, 126));
+            // bias of zero would be NaN.  (Below 2^-101 the layer's inputs are
+            // all zero and its biases as small; the bound and mul saturate only
+            // where every product is zero or rounds to it.)
+            const int e = __builtin_amdgcn_frexp_expf(__builtin_amdgcn_fmed3f(bound, 0x1p-101f, 0x1p126f));
+            mul = fminf(ldexpf(sc[2], ex - e), 0x1p126f);
             add = ldexpf(1.0f, 15 - e);
             ex = e;
             top = 0.0f;
