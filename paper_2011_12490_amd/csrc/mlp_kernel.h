@@ -536,12 +536,13 @@ struct Packer {
 //   that none exceeds 2^15.  What is lost then is below 2^-40 of that bound.
 // Heads whose rows or biases do not fit this (fits()) take the fp32 units.
 //
-// Bound by the matrix units (power-limited) with 7 VALU instructions per
-// output value beside them; one accumulator per tile (two, for the small and
+// What bounds it: with 8x128 heads the matrix pipe, 77 % busy at a
+// power-limited 1.64 GHz beside 4.95 VALU instructions per MFMA (7 per output
+// value); with 6x64 heads the VALU, 80 % active at 10.2 per MFMA.  One accumulator per tile (two, for the small and
 // the large products, would cost the 8x128 heads their second wave per SIMD).
 // 9.1 M samples of 8x128 heads: 18.2 ms on the fp32 units (142 TFLOP/s),
-// 5.9 ms here; pixels off the float64 render by 6.9e-6 before, 6.8e-6 now
-// (2.3e-7 and 1.9e-7 for opaque rays): the encoding's rounding, not the
+// 6.0 ms here; pixels off the float64 render by 6.9e-6 before, 6.8e-6 now
+// (2.3e-7 and 2.0e-7 for opaque rays): the encoding's rounding, not the
 // products', is what is left.
 template <class C>
 struct Split {

@@ -330,6 +330,8 @@ int main()
     expect(derf_gate_weights_count(0, 6, 16) == -1, "gate weights count of no heads");
     expect(derf_set_empty_heads(nullptr, nullptr) == DERF_ERR_INVALID_ARG,
            "empty heads without a handle");
+    expect(derf_head_arithmetic(nullptr, 0) == DERF_ERR_INVALID_ARG,
+           "head arithmetic without a handle");
     expect(derf_set_timing(nullptr, 1) == DERF_ERR_INVALID_ARG, "timing without a handle");
     expect(derf_set_encoding(nullptr, DERF_ENCODING_STORED) == DERF_ERR_INVALID_ARG,
            "encoding without a handle");

@@ -92,11 +92,13 @@ def _mfma(acc, a, b):
     return (acc.astype(np.float64) + b @ a.T).astype(F)
 
 
-def _split_layer(halves, xs):
-    """The three products of one layer, over the entries' scaled float32 values."""
+def _split_layer(halves, xs, low):
+    """The three products of one layer, over the entries' scaled float32 values
+    (low=False: without the entries' low halves)."""
     hi, lo = halves
     acc = np.zeros((len(xs), len(hi)), F)
     xh, xl = _split(xs)
+    xl = xl if low else 0 * xl
     for k in range(0, xs.shape[1], 16):
         s = slice(k, k + 16)
         for a, b in ((lo[:, s], xh[:, s]), (hi[:, s], xl[:, s]), (hi[:, s], xh[:, s])):
@@ -104,8 +106,9 @@ def _split_layer(halves, xs):
     return acc
 
 
-def split(arch, w, x, d, low=True):
-    """(density before its ReLU, colour logits) [m, 4] of the split form."""
+def split(arch, w, x, d, low=True, entries_low=True):
+    """(density before its ReLU, colour logits) [m, 4] of the split form; without
+    the low halves of the weights or of the layers' entries."""
     s = Scaled(arch, w, low)
     gx, gd = encode(x, arch.pos_freqs), encode(d, arch.dir_freqs)
     in_max = np.maximum(1, np.abs(x).max(1)).astype(F)
@@ -120,7 +123,7 @@ def split(arch, w, x, d, low=True):
         n1, b1 = s.bound[tag]
         bound = np.maximum((n1 * m + b1).astype(F), least)
         ne = np.maximum(_frexp(np.minimum(bound, F(2.0 ** 126))), -100)
-        acc = _split_layer(s.halves[tag], xs)
+        acc = _split_layer(s.halves[tag], xs, entries_low)
         out = (acc.astype(np.float64) * np.exp2((e - ne - s.shift[tag]).astype(np.float64))[:, None] +
                times(np.broadcast_to(s.v[tag][1], acc.shape), 15 - ne)).astype(F)
         out = np.maximum(out, 0)
@@ -133,7 +136,7 @@ def split(arch, w, x, d, low=True):
         h, e, m = layer("hidden%d" % l, h, e, m, least)
 
     def rows(tag, xs, e):
-        acc = _split_layer(s.halves[tag], xs)
+        acc = _split_layer(s.halves[tag], xs, entries_low)
         true = times(acc, e - 29)
         return (true.astype(np.float64) * s.factor[tag] + s.v[tag][1]).astype(F)
 

@@ -52,8 +52,8 @@ def _rms(x, axis=None):
 @pytest.mark.parametrize("kind,q,scale", CASES)
 def test_split_rounds_no_more_than_float32(arch, kind, q, scale):
     """The split form's outputs are no further from float64 than a float32
-    chain's, for weights that fit it; without the weights' low halves they miss
-    the bars above."""
+    chain's, for weights that fit it; without the low halves of the weights, or
+    of the layers' entries, they miss the bars above."""
     a = ARCHS[arch]
     w = _weights(a, kind, q, 3)
     if not split_form.Scaled(a, w).fits:
@@ -68,8 +68,9 @@ def test_split_rounds_no_more_than_float32(arch, kind, q, scale):
     f32 = _rms(split_form.chain(a, w, x, d, np.float32) - ref, 0) / size
     got = _rms(split_form.split(a, w, x, d) - ref, 0) / size
     assert (got <= 1.1 * f32).all(), (got, f32)
-    low = split_form.split(a, w, x, d, low=False) - ref
-    assert _rms(low[:, 0]) > 4 * SIGMA_RMS * size[0]
+    for lost in ({"low": False}, {"entries_low": False}):
+        low = split_form.split(a, w, x, d, **lost) - ref
+        assert _rms(low[:, 0]) > 4 * SIGMA_RMS * size[0]
 
 
 @pytest.mark.gpu
